@@ -133,8 +133,10 @@ bool gemm_act_fusable(int dtype, const GemmArgs& g);
 // act_mode 2 (0 if none).
 int gemm_act_parts();
 
-// Largest tile configuration index (contract's tile_cfg, plan entries).
+// Largest tile configuration index a caller may name (contract's tile_cfg,
+// plan entries), and the library's own choices beyond it.
 constexpr int GEMM_MAX_CFG = 25;
+constexpr int GEMM_CFG_WIDE = 26, GEMM_CFG_WIDE192 = 27;
 
 // Scratch bytes for a split-K contraction.
 inline size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t batch, int splits) {
@@ -155,5 +157,46 @@ int launch_gemm(int dtype, const GemmArgs& args, hipStream_t stream);
 // between 3/4 of the CUs and all of them one block; otherwise launch_gemm on
 // each, in order.
 int launch_gemm_pair(int dtype, const GemmArgs& a, const GemmArgs& b, hipStream_t stream);
+
+// ---- wide kernels (gemm_wide.hip): 256x256 or 256x192 tiles of four
+// 128x128 (128x96) waves, 64-wide k-steps.
+
+// Several contractions run by one grid, tiles dealt out over the XCDs.
+constexpr int GEMM_GROUP_MAX = 5;
+struct GemmGroup {
+    GemmArgs g[GEMM_GROUP_MAX];
+    int blocks[GEMM_GROUP_MAX];  // of each contraction (set by launch_wide_group)
+    int n;
+    int first_last;  // 1: the last contraction's blocks come first (its k range is the longest)
+    int spread;  // 1: every XCD takes an eighth of each contraction's tiles (grids of several rounds);
+                 // 0: each XCD takes one contiguous run of all tiles
+};
+// Whether the wide kernel of width bn (256 or 192) takes this contraction.
+bool gemm_wide_ok(const GemmArgs& g, int bn);
+void launch_wide(int dtype, const GemmArgs& g, int bn, hipStream_t st);
+void launch_wide_group(int dtype, const GemmGroup& grp, hipStream_t st);
+// Addition of the split-k partials of the group's split contractions, in
+// one launch.
+void launch_wide_reduce(const GemmGroup& grp, hipStream_t st);
+// Plans up to GEMM_GROUP_MAX independent contractions as one grid: weight
+// gradients (float output, both operands outer-contiguous) and, last, at
+// most one input gradient (A k-contiguous, B outer-contiguous, with a
+// residual).  Returns how many of them the group takes (all, or all but the
+// input gradient; 0: none), where the wide kernel takes them, no entry of
+// the running plan names one of them and the schedule is expected to be
+// shorter than one launch each.
+int plan_gemm_group(int dtype, const GemmArgs* gs, int n, GemmGroup* grp);
+// Launches a planned group; gemm_rowsum_parts() is that of gs[0].
+int launch_gemm_group(int dtype, const GemmGroup& grp, hipStream_t st);
+
+// The 16-bit kernels of a configured contraction (g.cfg and the fields the
+// launcher sets), and the paired lean 128x128 launch, per storage type.
+void launch_tiles_f16(const GemmArgs& g, hipStream_t st);
+void launch_tiles_bf16(const GemmArgs& g, hipStream_t st);
+// (the addition of split-k partials alone)
+void launch_reduce_f16(const GemmArgs& g, hipStream_t st);
+void launch_reduce_bf16(const GemmArgs& g, hipStream_t st);
+void launch_pair_f16(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st);
+void launch_pair_bf16(const GemmArgs& g0, const GemmArgs& g1, hipStream_t st);
 
 }  // namespace dm

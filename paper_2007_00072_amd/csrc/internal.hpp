@@ -86,7 +86,8 @@ int act_bwd_blocks(int64_t rows, bool transposed);
 // Layout and reduction choices of the fused operators for the running call:
 // its plan's, with every "library's choice" field resolved for this shape.
 struct FusedLayout {
-    bool dO_t;      // LayerNorm-2 backward writes dO^T, the Linear-2 weight gradient reads it
+    int dO_t;       // LayerNorm-2 backward writes dO^T, the Linear-2 weight gradient reads it:
+                    // 1 a plan asks for it, 2 where the weight gradients are launched one by one, 0 not
     bool dH_t;      // activation backward writes dH^T, the Linear-1 weight gradient reads it
     int ln_form;    // LayerNorm backward reduction form (0/1/2 as ln_bwd_uses_split)
     int ln_lanes;   // lanes per row of the row-form LayerNorm kernels (0 = by length)

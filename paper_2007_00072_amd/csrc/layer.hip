@@ -591,26 +591,49 @@ struct BiasParts {
     int cap;
     int parts;
 };
+// dX of segments [s0, s0 + ns): dX = dstk[:, segments] [W segments] + resid
+GemmArgs stacked_dx_args(const Dims& x, int layout, int64_t T, const void* dstk, int nseg, int seg0, int s0, int ns,
+                         const dm_layer_params* prm, void* dx, const void* resid) {
+    const int64_t H = x.H, I = x.I, P = x.P, HP = H * P;
+    const void* w[3] = {prm->wq, prm->wk, prm->wv};
+    Epilogue c = act_out(dx, layout, T, I);
+    c.resid = resid;
+    Operand Bw = opnd(w[s0], false, make_map((uint32_t)P, (uint32_t)H, H * I, I, 0));
+    for (int j = 0; j < ns; ++j) Bw.ptr[j] = w[s0 + j];
+    Bw.nseg = ns;
+    const void* a = B8(dstk, (size_t)x.es * (s0 - seg0) * HP);
+    return gemm(T, I, ns * HP, 1, opnd(a, true, linear_map(nseg * HP)), Bw, c);
+}
+
+// d[W segments] = dstk[:, segments]^T X, with partial row sums for the
+// input-bias gradients where `bias` asks for them
+GemmArgs stacked_dw_args(const Dims& x, int layout, const void* in, int64_t T, const void* dstk, int nseg, int seg0,
+                         int s0, int ns, const dm_layer_grads* g, const BiasParts* bias) {
+    const int64_t H = x.H, I = x.I, P = x.P, HP = H * P;
+    float* dw[3] = {g->dwq, g->dwk, g->dwv};
+    Epilogue cw = epi(dw[s0], make_map((uint32_t)P, (uint32_t)H, H * I, I, 0), linear_map(1), true, true);
+    for (int j = 0; j < ns; ++j) cw.ptr[j] = dw[s0 + j];
+    cw.nseg = ns; cw.seg_on_m = 1;
+    if (bias) {
+        // row (s, h, p) of dstk^T, partial sums in the same column order
+        cw.rsum = bias->part; cw.rsum_ld = (int)(ns * HP); cw.rsum_cap = bias->cap;
+    }
+    const void* a = B8(dstk, (size_t)x.es * (s0 - seg0) * HP);
+    return gemm(ns * HP, I, T, 1, opnd(a, false, linear_map(nseg * HP)), act_kn(in, layout, T, I), cw);
+}
+
 int project_stacked_bwd(const Dims& x, int layout, const void* in, int64_t T, const void* dstk, int nseg, int seg0,
                         const ProjGroup* grp, int n, const dm_layer_params* prm, void* dx, const dm_layer_grads* g,
                         const void* resid, hipStream_t st, const GemmArgs* pair = nullptr,
                         BiasParts* bias = nullptr) {
-    const int64_t H = x.H, I = x.I, P = x.P, HP = H * P, ld = nseg * HP;
-    const IdxMap wmap = make_map((uint32_t)P, (uint32_t)H, H * I, I, 0);
-    const void* w[3] = {prm->wq, prm->wk, prm->wv};
-    float* dw[3] = {g->dwq, g->dwk, g->dwv};
     {
         TraceScope t_("B18 qkv_dx", st);
         for (int i = 0; i < n; ++i) {
             const int s0 = grp[i].s0, ns = grp[i].s1 - grp[i].s0;
             if (i > 0) trace_next(grp[i].sub);
-            Epilogue c = act_out(dx, layout, T, I);
-            c.resid = i == 0 ? resid : dx;
-            Operand Bw = opnd(w[s0], false, wmap);
-            for (int j = 0; j < ns; ++j) Bw.ptr[j] = w[s0 + j];
-            Bw.nseg = ns;
-            const void* a = B8(dstk, (size_t)x.es * (s0 - seg0) * HP);
-            DM_TRY(launch_gemm(x.dtype, gemm(T, I, ns * HP, 1, opnd(a, true, linear_map(ld)), Bw, c), st));
+            DM_TRY(launch_gemm(x.dtype,
+                               stacked_dx_args(x, layout, T, dstk, nseg, seg0, s0, ns, prm, dx, i == 0 ? resid : dx),
+                               st));
         }
     }
     TraceScope t_(pair ? "B12+19 out_dw+qkv_dw" : "B19 qkv_dw", st);
@@ -619,15 +642,7 @@ int project_stacked_bwd(const Dims& x, int layout, const void* in, int64_t T, co
     for (int i = 0; i < n; ++i) {
         const int s0 = grp[i].s0, ns = grp[i].s1 - grp[i].s0;
         if (i > 0) trace_next(grp[i].sub);
-        Epilogue cw = epi(dw[s0], wmap, linear_map(1), true, true);
-        for (int j = 0; j < ns; ++j) cw.ptr[j] = dw[s0 + j];
-        cw.nseg = ns; cw.seg_on_m = 1;
-        if (want_bias) {
-            // row (s, h, p) of dstk^T, partial sums in the same column order
-            cw.rsum = bias->part; cw.rsum_ld = (int)(ns * HP); cw.rsum_cap = bias->cap;
-        }
-        const void* a = B8(dstk, (size_t)x.es * (s0 - seg0) * HP);
-        const GemmArgs gw = gemm(ns * HP, I, T, 1, opnd(a, false, linear_map(ld)), act_kn(in, layout, T, I), cw);
+        const GemmArgs gw = stacked_dw_args(x, layout, in, T, dstk, nseg, seg0, s0, ns, g, want_bias ? bias : nullptr);
         if (i == 0 && pair) DM_TRY(launch_gemm_pair(x.dtype, gw, *pair, st));
         else DM_TRY(launch_gemm(x.dtype, gw, st));
         if (want_bias) bias->parts = gemm_rowsum_parts();
@@ -816,7 +831,25 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
     // the Linear-2 weight gradient reads one operand contiguous along the
     // tokens (the plan's layout choice; on by default)
     void* dOT = B8(ws, e.dOT);
-    const bool have_dOT = fl.dO_t;
+    // The weight gradients (and the input gradient of the Q/K/V projections)
+    // are read by no later step of the backward, so at sizes where it pays
+    // they wait for its end and share one grid of 256x256 tiles: BERT-large
+    // with 4096 tokens has 192 + 64 such tiles, one per CU, where each
+    // contraction alone leaves three quarters of the CUs idle on that tile
+    // and is bound by LDS reads on 128x128 ones.  (A plan that asks for a
+    // transposed copy keeps separate launches.)
+    BiasParts bias = {part, colsum_blocks(T), 0};
+    const GemmArgs tail[5] = {
+        stacked_dw_args(x, DM_BJI, x_in, T, dqkv, 3, 0, 0, 3, g, &bias),
+        out_dw_args(x, gamma, dAO, DM_BJI, g->dwo),
+        gemm(I, F, T, 1, opnd(dO, false, linear_map(I)), opnd(abuf, false, linear_map(F)),
+             epi(g->dw2, linear_map(F), linear_map(1), true, true)),
+        gemm(F, I, T, 1, opnd(dH, false, linear_map(F)), opnd(y1, false, linear_map(I)),
+             epi(g->dw1, linear_map(I), linear_map(1), true, true)),
+        stacked_dx_args(x, DM_BJI, T, dqkv, 3, 0, 0, 3, prm, dx, dS1)};
+    GemmGroup group;
+    const int grouped = x.qkv_fusion == 0 && fl.dO_t != 1 && !fl.dH_t ? plan_gemm_group(dt, tail, 5, &group) : 0;
+    const bool have_dOT = !grouped && fl.dO_t != 0;
     l2.dsub_t = have_dOT ? dOT : nullptr;
     {
         TraceScope t_("B1-2 ln2_bwd", st);
@@ -848,7 +881,7 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
         TraceScope t_("B3 linear2_dx", st);
         DM_TRY(launch_gemm(dt, g3, st));
     }
-    {
+    if (!grouped) {
         TraceScope t_("B4 linear2_dw", st);
         const Operand a_op = have_dOT ? opnd(dOT, true, linear_map(T)) : opnd(dO, false, linear_map(I));
         DM_TRY(launch_gemm(dt,
@@ -870,7 +903,7 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
                                 epi(dY1f, linear_map(I), linear_map(1), true, false)),
                            st));
     }
-    {
+    if (!grouped) {
         TraceScope t_("B7 linear1_dw", st);
         const Operand a_op = dHT ? opnd(dHT, true, linear_map(T)) : opnd(dH, false, linear_map(F));
         DM_TRY(launch_gemm(dt,
@@ -895,13 +928,21 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
     DM_TRY(attention_core_bwd(x, scaler_of(d), make_drop(d->p_attn, d->seed, 0, d->layer_id), dAO, DM_BJI, q, k, v,
                               prob, alpha, gamma, gamma32, prm->wo, nullptr, dgamma, dalpha, dbeta, dqkv, ld,
                               B8(dqkv, (size_t)es * I), ld, B8(dqkv, (size_t)es * 2 * I), ld, st));
-    // Q, K, V dX (fused) + encoder-input residual; Q, K, V dW (fused) with Out dW
-    const GemmArgs out_dw = out_dw_args(x, gamma, dAO, DM_BJI, g->dwo);
-    // (the Q/K/V weight gradient also takes partial column sums of dQKV for
-    // the input-bias gradients (B20), where its kernel allows)
+    // Q, K, V dX (fused) + encoder-input residual; Q, K, V dW (fused) with
+    // Out dW (the Q/K/V weight gradient also takes partial column sums of
+    // dQKV for the input-bias gradients (B20), where its kernel allows)
+    if (grouped) {
+        if (grouped < 5) {
+            TraceScope t_("B18 qkv_dx", st);
+            DM_TRY(launch_gemm(dt, tail[4], st));
+        }
+        TraceScope t_(grouped < 5 ? "B4+7+12+19 weight_grads" : "B4+7+12+18+19 weight_grads+qkv_dx", st);
+        DM_TRY(launch_gemm_group(dt, group, st));
+        bias.parts = gemm_rowsum_parts();
+    } else {
+        DM_TRY(project_fused_bwd(x, DM_BJI, x_in, dqkv, prm, dx, g, dS1, st, &tail[1], &bias));
+    }
     const int ncs = colsum_blocks(T);
-    BiasParts bias = {part, ncs, 0};
-    DM_TRY(project_fused_bwd(x, DM_BJI, x_in, dqkv, prm, dx, g, dS1, st, &out_dw, &bias));
     // input-bias partial sums otherwise
     if (bias.parts == 0) {
         TraceScope t20("B20 qkv_bias_grad", st);

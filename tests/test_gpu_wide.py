@@ -1,0 +1,113 @@
+"""The wide contraction kernels (256x256 and 256x192 tiles of four waves, the
+library's own choice for large outputs) and the grouped launch of the
+backward's weight gradients, at the sizes where they can go wrong: one, two
+and three k-steps (fewer than the five LDS slots hold), k-rows past the end
+of an outer-contiguous pair, ragged last tiles, split partials, every
+operand layout; and layers whose group is split, spread over several
+rounds, or takes the input gradient in."""
+import pytest
+import torch
+
+from paper_2007_00072_amd import lib
+from paper_2007_00072_amd.inputs import make_tensor
+from test_gpu_layer import check_encoder, run_encoder, small
+from test_gpu_plan import _launches
+
+pytestmark = pytest.mark.gpu
+DT = {"f16": (lib.DM_F16, torch.float16, 2.0 ** -11), "bf16": (lib.DM_BF16, torch.bfloat16, 2.0 ** -8)}
+
+
+def contraction(dtype, a_trans, b_trans, M, N, K, bias=False, out_f32=False, splits=1):
+    code, td, _ = DT[dtype]
+    A = make_tensor((K, M) if a_trans else (M, K), dtype, 3).cuda()
+    B = make_tensor((N, K) if b_trans else (K, N), dtype, 4).cuda()
+    bv = make_tensor((N,), dtype, 5).cuda() if bias else None
+    # (a band of rows after the output that no store may reach)
+    C = torch.full((M + 8, N), 7.0, dtype=torch.float32 if out_f32 else td, device="cuda")
+    ws = torch.empty(splits * M * N if splits > 1 else 1, dtype=torch.float32, device="cuda")
+    lib.plan_log(True)
+    lib.contract(code, 1, M, N, K, 1.0, A, int(a_trans), 0, B, int(b_trans), 0, bv, C, int(out_f32), 0, -1, splits,
+                 ws if splits > 1 else None, ws.numel() * 4 if splits > 1 else 0)
+    torch.cuda.synchronize()
+    lib.plan_log(False)
+    assert (C[M:] == 7.0).all()
+    a = (A.t() if a_trans else A).float()
+    b = (B.t() if b_trans else B).float()
+    ref = a.double() @ b.double().contiguous()
+    if bias:
+        ref = ref + bv.double()
+    # fp32 accumulation of K products of magnitude ~1, one rounding to the
+    # output type: |err| <= u |ref| + K 2^-23 (rms of a product's sum sqrt K)
+    u = 2.0 ** -23 if out_f32 else DT[dtype][2]
+    bound = u * ref.abs() + (K ** 0.5) * 2.0 ** -20 + K * 2.0 ** -23
+    worst = ((C[:M].double() - ref).abs() / bound).max().item()
+    assert worst <= 1.0, worst
+
+
+# 15 x 14 tiles of 256: 3/4 of the CUs have one
+@pytest.mark.parametrize("a_trans,b_trans", [(False, True), (False, False), (True, True), (True, False)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K", [64, 128, 192, 320])
+def test_wide_contract(dtype, a_trans, b_trans, K):
+    contraction(dtype, a_trans, b_trans, 3720, 3464, K, bias=True)
+
+
+@pytest.mark.parametrize("K", [8, 56, 72, 200, 328])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_wide_contract_ragged_k(dtype, K):
+    # both operands outer-contiguous: the last step's missing k-rows are zeros
+    contraction(dtype, True, False, 3720, 3464, K, out_f32=dtype == "f16")
+
+
+@pytest.mark.parametrize("a_trans", [False, True])
+def test_wide_contract_192(a_trans):
+    # 16 x 15 tiles of 256 x 192 fit one round where 256 x 256 leaves CUs idle
+    contraction("f16", a_trans, True, 4088, 2880, 256, bias=True)
+
+
+def grads_label(labels):
+    return [lab for lab in labels if lab.startswith("B4+7+12")]
+
+
+@pytest.mark.parametrize("name,shape,want", [
+    # 192 weight-gradient tiles, k of 512 tokens, input gradient on its own
+    ("bert_large_f16", dict(B=4, J=128, K=128, H=16, P=64, W=64, I=1024, F=4096), "B4+7+12+19 weight_grads"),
+    # ragged tokens: 1000 = 15 steps of 64 and 40
+    ("bert_base_bf16", dict(B=5, J=200, K=200, H=16, P=64, W=64, I=1024, F=4096), None),
+])
+def test_layer_with_grouped_weight_gradients(name, shape, want):
+    wl = small(name, **shape)
+    _, labels = _launches(wl)
+    assert grads_label(labels) and "B4 linear2_dw" not in labels and "B12+19 out_dw+qkv_dw" not in labels, labels
+    if want:
+        assert want in labels
+    check_encoder(wl, layer=1)
+
+
+@pytest.mark.parametrize("name,shape", [
+    # 192 tiles, unsplit
+    ("bert_large_f16", dict(B=4, J=128, K=128, H=16, P=64, W=64, I=1024, F=4096)),
+    # BERT-base widths, 12288 tokens: 108 tiles, so the token sums are split
+    # and the grid has more than one round
+    ("bert_base_bf16", dict(B=96, J=128, K=128, H=12, P=64, W=64, I=768, F=3072)),
+])
+def test_group_and_separate_launches_agree(name, shape):
+    # a plan entry that names one of the contractions separates the group
+    wl = small(name, **shape)
+    T, I, F = shape["B"] * shape["J"], shape["I"], shape["F"]
+    L0, _, _, _, y0, dx0 = run_encoder(wl)
+    g0 = {n: t.clone() for n, t in L0.grads.items()}
+    recs, labels = _launches(wl)
+    assert grads_label(labels), labels
+    dw1 = next(r for r in recs if (r.M, r.N, r.K) == (F, I, T) and not r.a_kcontig)
+    assert (dw1.splits > 1) == (T > 4096)
+    plan = lib.Plan([lib.ContractChoice(*dw1.key(), 15, 1)], 0)
+    _, labels = _launches(wl, plan)
+    assert not grads_label(labels) and "B7 linear1_dw" in labels
+    L1, _, _, _, y1, dx1 = run_encoder(wl, plan=plan)
+    assert torch.equal(y0, y1)
+    # (the input gradient's sums of 3 I products in another order, one rounding to the storage type)
+    assert (dx0.float() - dx1.float()).norm() <= 2.0 ** -8 * dx1.float().norm()
+    for n, t in L1.grads.items():
+        # T products per sum, fp32 accumulation in another order
+        assert (g0[n] - t).abs().max().item() <= T ** 0.5 * 2.0 ** -20 * max(t.abs().max().item(), 1e-3), n
