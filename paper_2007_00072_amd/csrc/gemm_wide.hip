@@ -86,18 +86,20 @@ __device__ __forceinline__ void rowsum_mfma(floatx4& c, bf16x8 o, bf16x8 a) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(o), "v"(a));
 }
 
-// 16 bytes per lane from base + voff + soff to LDS at lds_byte + 16 lane;
-// records = 0 reads zeros.
-__device__ __forceinline__ void copy16(uint64_t base, uint32_t records, uint32_t voff, uint32_t soff,
-                                       uint32_t lds_byte) {
-    u32x4 rsrc;
-    rsrc[0] = __builtin_amdgcn_readfirstlane((uint32_t)base);
-    rsrc[1] = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xffffu);
-    rsrc[2] = __builtin_amdgcn_readfirstlane(records);
-    rsrc[3] = 0x00020000u;
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc),
-                 "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(__builtin_amdgcn_readfirstlane(lds_byte))
-                 : "memory");
+// 16 bytes per lane from the buffer's base + voff + soff to LDS at m0 + 16
+// lane.  m0 is set one MFMA ahead of the copy (set_m0, then copy16 after the
+// next MFMA): one wave issues an instruction every 4 cycles, so with its 16
+// an MFMA covers three others, and a copy with all of its scalar work in
+// one place held up the MFMAs (k-loop 26.0 against 22.5 us per 1024 of k
+// with outer-contiguous operands).
+__device__ __forceinline__ void set_m0(uint32_t slot, uint32_t ofs) {
+    asm volatile("s_add_u32 m0, %0, %1" ::"s"(slot), "i"(ofs) : "scc", "memory");
+}
+__device__ __forceinline__ void copy16(u32x4 rsrc, uint32_t voff, uint32_t soff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ u32x4 buffer_at(uint64_t base, uint32_t records) {
+    return u32x4{(uint32_t)base, (uint32_t)(base >> 32) & 0xffffu, records, 0x00020000u};
 }
 template <int N>
 __device__ __forceinline__ void wait_copies() {
@@ -111,32 +113,67 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
            ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32);
 }
 
+// Each operand: init, then per k-step `Step` (scalar state: at(first step),
+// advanced by next()), and copy(step, i) of its NV copies.
+//
 // k-contiguous operand, R rows: LDS row r holds 8 chunks of 16 bytes,
 // logical chunk c at c ^ ((r >> 1) & 7) (the 16 rows of one fragment read
 // cover all 64 banks once).  Copy i of wave w brings rows 32 i + 8 w .. + 7,
-// which any row map with a lowest radix that is a multiple of 8 keeps
-// evenly spaced: one scalar base per copy, one lane offset for all.
-template <typename T, int R, bool KC>
+// which any row map with a lowest radix that is a multiple of 8 keeps evenly
+// spaced and in one segment.  A single-segment operand (A) has one scalar
+// base and a lane offset per copy; one of several segments (B: stacked
+// weights) a base per copy and one lane offset.  (Bases per copy for both
+// did not fit the scalar registers: they spilled, and a base read back just
+// before the copy that uses it needs wait states that the compiler does not
+// insert before assembly.)
+template <typename T, int R, bool KC, bool SEG>
 struct WideOp;
 template <typename T, int R>
-struct WideOp<T, R, true> {
+struct WideOp<T, R, true, false> {
     static constexpr int NV = R / 32;
-    uint64_t base[NV];
-    uint32_t vo;
-    __device__ __forceinline__ void init(const Operand& op, int kb, int o0, int omax, int w, int lane) {
+    uint64_t base;
+    uint32_t vo[NV];
+    __device__ __forceinline__ void init(const Operand& op, int kb, int, int o0, int omax, int w, int lane) {
+        base = (uint64_t)(reinterpret_cast<const T*>(op.ptr[0]) + kb);
+        const uint32_t vl =
+            (uint32_t)((lane >> 3) * op.row.s0 * 2) + (uint32_t)(((lane & 7) ^ ((w * 4 + (lane >> 4)) & 7)) * 16);
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int row = min(o0 + i * 32 + w * 8, omax - 8);  // (rows past the end: any valid ones)
             int seg = 0;
-            const int64_t off = map_off(op.row, (uint32_t)row, op.nseg, &seg);
-            base[i] = uniform64((uint64_t)(reinterpret_cast<const T*>(pick(op.ptr, seg)) + off + kb));
+            vo[i] = vl + (uint32_t)(map_off(op.row, (uint32_t)row, 1, &seg) * 2);
         }
-        vo = (uint32_t)((lane >> 3) * op.row.s0 * 2) + (uint32_t)(((lane & 7) ^ ((w * 4 + (lane >> 4)) & 7)) * 16);
     }
-    struct Step {};
-    __device__ __forceinline__ Step at(const Operand&, int, int, int, int) const { return Step{}; }
-    __device__ __forceinline__ void copy(const Step&, int i, int s, uint32_t slot, int w) const {
-        copy16(base[i], 0xffffffffu, vo, (uint32_t)(s * WK * 2), slot + (uint32_t)(i * 256 + w * 64) * 16u);
+    struct Step { uint32_t soff; };
+    __device__ __forceinline__ Step first(const Operand&) const { return Step{0u}; }
+    __device__ __forceinline__ void next(const Operand&, Step& t) const { t.soff += WK * 2; }
+    __device__ __forceinline__ void copy(const Step& t, int i) const {
+        copy16(buffer_at(base, 0xffffffffu), vo[i], t.soff);
+    }
+    __device__ __forceinline__ static u32x4 frag(const unsigned char* lds, int ob, int q, int lane) {
+        return WideOp<T, R, true, true>::frag(lds, ob, q, lane);
+    }
+};
+template <typename T, int R>
+struct WideOp<T, R, true, true> {
+    static constexpr int NV = R / 32;
+    uint64_t base[NV];
+    uint32_t vo;
+    __device__ __forceinline__ void init(const Operand& op, int kb, int, int o0, int omax, int w, int lane) {
+        vo = (uint32_t)((lane >> 3) * op.row.s0 * 2) + (uint32_t)(((lane & 7) ^ ((w * 4 + (lane >> 4)) & 7)) * 16);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int row = min(o0 + i * 32 + w * 8, omax - 8);
+            int seg = 0;
+            const int64_t off = map_off(op.row, (uint32_t)row, op.nseg, &seg);
+            base[i] = uniform64((uint64_t)(reinterpret_cast<const T*>(pick(op.ptr, seg)) + off + kb)) & 0xffffffffffffull;
+        }
+    }
+    struct Step { uint32_t soff; };
+    __device__ __forceinline__ Step first(const Operand&) const { return Step{0u}; }
+    __device__ __forceinline__ void next(const Operand&, Step& t) const { t.soff += WK * 2; }
+    __device__ __forceinline__ void copy(const Step& t, int i) const {
+        copy16(u32x4{(uint32_t)base[i], (uint32_t)(base[i] >> 32), 0xffffffffu, 0x00020000u}, vo, t.soff);
     }
     // lane l: row ob + l % 16, k = 32 q + 8 (l / 16) .. + 7
     __device__ __forceinline__ static u32x4 frag(const unsigned char* lds, int ob, int q, int lane) {
@@ -149,36 +186,43 @@ struct WideOp<T, R, true> {
 // transposing ds_read_b64_tr_b16 (within 16 lanes, lane i receives element
 // i % 4 of the 8-byte pieces addressed by lanes i / 4 + 4 j), whose eight
 // 4-row groups of two lane groups then fall on different banks.  Copy i of
-// wave w brings k-rows 8 i + 2 w, + 1; k-rows past the end are read as
-// zeros (k is a multiple of 8, so a copy is wholly inside or outside).
-template <typename T, int R>
-struct WideOp<T, R, false> {
+// wave w brings k-rows 8 i + 2 w, + 1.  The buffer of a step ends with its
+// last valid k-row, and what lies past a buffer's end is read as zeros.
+template <typename T, int R, bool SEG>
+struct WideOp<T, R, false, SEG> {
     static_assert(R == 256, "k-rows of 32 chunks");
     static constexpr int NV = 8;
-    uint32_t vo[2];
+    uint32_t vo[NV];
+    int k0, ke, o0;
+    uint32_t pitch;  // bytes of a k-row
+    bool plain;      // one stride for every k-row
     __device__ __forceinline__ static int swz(int r) { return 2 * (r & 3) + 8 * ((r >> 3) & 1); }
-    __device__ __forceinline__ void init(const Operand& op, int, int o0, int omax, int w, int lane) {
+    __device__ __forceinline__ void init(const Operand& op, int kb, int ke_, int o0_, int omax, int w, int lane) {
+        k0 = kb; ke = ke_; o0 = o0_;
+        pitch = (uint32_t)(op.row.s0 * 2);
+        plain = op.row.r0 == 0;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int kr = w * 2 + (lane >> 5), c = (lane & 31) ^ swz(p * 8 + kr);
+        for (int i = 0; i < NV; ++i) {
+            const int kr = i * 8 + w * 2 + (lane >> 5), c = (lane & 31) ^ swz(kr);
             const int o = o0 + c * 8 < omax ? c * 8 : 0;  // (columns past the end: any valid ones)
-            vo[p] = (uint32_t)(kr * op.row.s0 * 2) + (uint32_t)(o * 2);
+            vo[i] = (uint32_t)kr * pitch + (uint32_t)(o * 2);
         }
     }
-    struct Step { uint64_t base; int rem; uint32_t ld8; };
-    __device__ __forceinline__ Step at(const Operand& op, int kb, int ke, int o0, int s) const {
-        const int k = kb + s * WK;
+    struct Step { uint64_t base; int k; };
+    __device__ __forceinline__ uint64_t base_of(const Operand& op, int k) const {
         int seg = 0;
         const int64_t off = map_off(op.row, (uint32_t)k, op.nseg, &seg);
-        Step t;
-        t.base = uniform64((uint64_t)(reinterpret_cast<const T*>(pick(op.ptr, seg)) + off + o0));
-        t.rem = ke - k;
-        t.ld8 = (uint32_t)(op.row.s0 * 16);
-        return t;
+        return uniform64((uint64_t)(reinterpret_cast<const T*>(pick(op.ptr, seg)) + off + o0));
     }
-    __device__ __forceinline__ void copy(const Step& t, int i, int, uint32_t slot, int w) const {
-        copy16(t.base, i * 8 < t.rem ? 0xffffffffu : 0u, vo[i & 1], (uint32_t)i * t.ld8,
-               slot + (uint32_t)(i * 256 + w * 64) * 16u);
+    __device__ __forceinline__ Step first(const Operand& op) const { return Step{base_of(op, k0), k0}; }
+    __device__ __forceinline__ void next(const Operand& op, Step& t) const {
+        t.k += WK;
+        if (plain) t.base += (uint64_t)pitch * WK;
+        else if (t.k < ke) t.base = base_of(op, t.k);
+    }
+    __device__ __forceinline__ void copy(const Step& t, int i) const {
+        // (a step that is copied has at least 8 valid rows)
+        copy16(buffer_at(t.base, (uint32_t)min(ke - t.k, WK) * pitch), vo[i], 0u);
     }
     __device__ __forceinline__ static u32x4 frag(const unsigned char* lds, int ob, int q, int lane) {
         typedef short s4 __attribute__((ext_vector_type(4)));
@@ -204,15 +248,15 @@ template <typename T, int BN, bool AKC, bool BKC, bool RSUM>
 __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem, int tm, int tn, int sidx,
                                           floatx4 (&acc)[8][BN / 32], floatx4 (&rs)[RSUM ? 8 : 1]) {
     constexpr int FM = 8, FN = BN / 32, NM = FM * FN, NR = FM + FN;
-    typedef WideOp<T, WBM, AKC> OA;
-    typedef WideOp<T, BN, BKC> OB;
+    typedef WideOp<T, WBM, AKC, false> OA;
+    typedef WideOp<T, BN, BKC, true> OB;
     typedef typename WMfma<T>::frag frag;
     // positions: MFMAs of the second slice before the barrier; MFMAs per
     // fragment read in the first and in the second slice; per copy of A
     // (first slice) and of B (second slice)
     constexpr int BP = 8, R0 = NM / NR < 3 ? NM / NR : 3, R1 = (NM - BP) / NR < 3 ? (NM - BP) / NR : 3;
     constexpr int CA = NM / OA::NV, CB = (NM - BP) / OB::NV;
-    static_assert(R0 * NR <= NM && R1 * NR <= NM - BP && 2 + (OB::NV - 1) * CB < NM - BP, "schedule");
+    static_assert(CA > 2 && CB > 2 && R0 * NR <= NM && R1 * NR <= NM - BP && 2 + (OB::NV - 1) * CB < NM - BP, "schedule");
 
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = w >> 1, wn = w & 1;
@@ -220,9 +264,9 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
     const int kb = sidx * g.kper, ke = min(g.K, kb + g.kper);
     OA da;
     OB db;
-    da.init(g.a, kb, m0, g.M, w, lane);
-    db.init(g.b, kb, n0, g.N, w, lane);
-    const uint32_t base = lds_offset(smem);
+    da.init(g.a, kb, ke, m0, g.M, w, lane);
+    db.init(g.b, kb, ke, n0, g.N, w, lane);
+    const uint32_t base = lds_offset(smem) + (uint32_t)w * 1024u;  // of the wave's part of a copy
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -259,16 +303,27 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
         }
     };
     // steps 0 and 1 (slots 0..3)
+    auto ta = da.first(g.a);
+    auto tb = db.first(g.b);
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < 2; ++s) {
         if (s < nk) {
-            const auto ta = da.at(g.a, kb, ke, m0, s);
-            const auto tb = db.at(g.b, kb, ke, n0, s);
 #pragma unroll
-            for (int i = 0; i < OA::NV; ++i) da.copy(ta, i, s, base + (uint32_t)(2 * s) * SLOT, w);
+            for (int i = 0; i < OA::NV; ++i) {
+                set_m0(base + (uint32_t)(2 * s) * SLOT, (uint32_t)i * 4096u);
+                asm volatile("s_nop 0" ::: "memory");
+                da.copy(ta, i);
+            }
 #pragma unroll
-            for (int i = 0; i < OB::NV; ++i) db.copy(tb, i, s, base + (uint32_t)(2 * s + 1) * SLOT, w);
+            for (int i = 0; i < OB::NV; ++i) {
+                set_m0(base + (uint32_t)(2 * s + 1) * SLOT, (uint32_t)i * 4096u);
+                asm volatile("s_nop 0" ::: "memory");
+                db.copy(tb, i);
+            }
         }
+        da.next(g.a, ta);
+        db.next(g.b, tb);
+    }
     if (nk >= 2) wait_copies<OA::NV + OB::NV>();
     else wait_copies<0>();
     __builtin_amdgcn_s_barrier();
@@ -283,13 +338,13 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
         constexpr bool MORE = decltype(more_c)::value;  // step s + 2 exists
         const uint32_t sB = adv(sA, 1), sA1 = adv(sA, 2), sB1 = adv(sA, 3), sA2 = adv(sA, 4);
         const unsigned char *A = smem + sA, *B = smem + sB, *A1 = smem + sA1, *B1 = smem + sB1;
-        const auto ta = da.at(g.a, kb, ke, m0, s + 2);
-        const auto tb = db.at(g.b, kb, ke, n0, s + 2);
+        const uint32_t toA = base + sA2, toB = base + sA;
 #pragma unroll
         for (int t = 0; t < NM; ++t) {
             mma(0, t);
             if (t % R0 == 0 && t / R0 < NR) read(1, A, B, 1, t / R0);
-            if (MORE && t % CA == 1 && t / CA < OA::NV) da.copy(ta, t / CA, s + 2, base + sA2, w);
+            if (MORE && t % CA == 1 && t / CA < OA::NV) set_m0(toA, (uint32_t)(t / CA) * 4096u);
+            if (MORE && t % CA == 2 && t / CA < OA::NV) da.copy(ta, t / CA);
             __builtin_amdgcn_sched_barrier(0);
         }
         row_sums(0, 2 * s);
@@ -305,6 +360,7 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+        if (MORE) da.next(g.a, ta);
         __builtin_amdgcn_sched_barrier(0);
         // (after the last step the reads are of a stale slot, unused)
 #pragma unroll
@@ -312,9 +368,11 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
             mma(1, t);
             const int u = t - BP;
             if (u % R1 == 0 && u / R1 < NR) read(0, A1, B1, 0, u / R1);
-            if (MORE && u >= 2 && (u - 2) % CB == 0 && (u - 2) / CB < OB::NV) db.copy(tb, (u - 2) / CB, s + 2, base + sA, w);
+            if (MORE && u >= 1 && (u - 1) % CB == 0 && (u - 1) / CB < OB::NV) set_m0(toB, (uint32_t)((u - 1) / CB) * 4096u);
+            if (MORE && u >= 2 && (u - 2) % CB == 0 && (u - 2) / CB < OB::NV) db.copy(tb, (u - 2) / CB);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (MORE) db.next(g.b, tb);
         row_sums(1, 2 * s + 1);
         sA = sA1;
     };
@@ -371,148 +429,191 @@ __device__ __forceinline__ void wide_store_f32(const GemmArgs& g, const floatx4 
     }
 }
 
-// Outputs in the storage type: 16 rows at a time through the wave's own LDS
-// (a wave's LDS accesses run in order, so no barrier), read back as 16-byte
-// row pieces.  ACT 1 / 2: the activation operators of Epilogue::act_mode on
-// each piece.  RESID: staged in fp32, the residual added before rounding.
-template <typename T, int FN, int ACT, bool RESID>
-__device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&acc)[8][FN], int mw, int nw,
-                                           unsigned char* region) {
-    constexpr int WN = FN * 16, ES = RESID ? 4 : 2;
-    constexpr int PITCH = WN * ES + 16;                 // bytes: 16 rows start on different bank groups
+// Outputs in the storage type with a residual: 16 rows at a time staged in
+// fp32 through the wave's own LDS (a wave's LDS accesses run in order, so no
+// barrier), read back as row pieces, the residual added before rounding.
+template <typename T, int FN>
+__device__ __forceinline__ void wide_store_resid(const GemmArgs& g, const floatx4 (&acc)[8][FN], int mw, int nw,
+                                                 unsigned char* region) {
+    constexpr int WN = FN * 16, PITCH = WN * 4 + 16;
     constexpr int VPR = WN / 8, RPI = 64 / VPR, NPASS = (16 + RPI - 1) / RPI;
     const int lane = threadIdx.x & 63;
     const Epilogue& e = g.c;
     const int rr0 = lane / VPR, vc = (lane % VPR) * 8, n = nw + vc;
     const bool lane_on = lane < RPI * VPR && n < g.N;
-    int nsg = 0;
-    const int64_t noff = map_off(e.nmap, (uint32_t)(n < g.N ? n : 0), e.seg_on_m ? 1 : e.nseg, &nsg);
-    // bias: four consecutive columns per 16-column block of a lane
-    float bn[FN][4];
-    if (!RESID && ACT == 0) {
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) bn[j][r] = 0.f;
-        if (e.bias[0]) {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                // (four consecutive indices stay inside one digit: the bias
-                // map's lowest radix is a multiple of 8)
-                const int c = nw + j * 16 + 4 * (lane >> 4);
-                int sg = 0;
-                const int64_t bo = map_off(e.bias_map, (uint32_t)(c < g.N ? c : 0), e.bias_nseg, &sg);
-                const T* bp = reinterpret_cast<const T*>(pick(e.bias, sg)) + bo;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) bn[j][r] = to_f(bp[r * e.bias_map.s0]);
-            }
-        }
-    }
-    u32x4 bias_raw = {0u, 0u, 0u, 0u};
-    if constexpr (ACT != 0)
-        if (lane_on) bias_raw = *reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(e.act_bias) + n);
-    float cs[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) cs[q] = 0.f;
+    int d = 0;
+    const int64_t noff = map_off(e.nmap, (uint32_t)(n < g.N ? n : 0), 1, &d);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int mb = mw + i * 16;
         if (mb >= g.M) break;
-        unsigned char* wr = region + (lane & 15) * PITCH + (lane >> 4) * 4 * ES;
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            if constexpr (RESID) {
-                *reinterpret_cast<floatx4*>(wr + j * 64) = acc[i][j];
-            } else {
-                T v[4];
+        for (int j = 0; j < FN; ++j)
+            *reinterpret_cast<floatx4*>(region + (lane & 15) * PITCH + (lane >> 4) * 16 + j * 64) = acc[i][j];
+        u32x4 hv[NPASS];
+        int64_t off[NPASS];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = from_f<T>(ACT == 0 ? acc[i][j][r] + bn[j][r] : acc[i][j][r]);
-                *reinterpret_cast<u32x2*>(wr + j * 32) = __builtin_bit_cast(u32x2, v);
-            }
-        }
-        // operands of the block's pieces, all requested before the first use
-        u32x4 hv[ACT == 2 || RESID ? NPASS : 1];
-        if constexpr (ACT == 2 || RESID) {
-#pragma unroll
-            for (int p = 0; p < NPASS; ++p) {
-                const int rr = p * RPI + rr0, m = mb + rr;
-                hv[p] = u32x4{0u, 0u, 0u, 0u};
-                if (lane_on && rr < 16 && m < g.M) {
-                    const T* src;
-                    if constexpr (RESID) {
-                        int d = 0;
-                        src = reinterpret_cast<const T*>(e.resid) + map_off(e.mmap, (uint32_t)m, 1, &d) + noff;
-                    } else {
-                        src = reinterpret_cast<const T*>(e.act_in) + (int64_t)m * g.ldc + n;
-                    }
-                    hv[p] = *reinterpret_cast<const u32x4*>(src);
-                }
-            }
-        }
-        auto pass = [&](int p, u32x4 h) {
+        for (int p = 0; p < NPASS; ++p) {
             const int rr = p * RPI + rr0, m = mb + rr;
-            if (!lane_on || rr >= 16 || m >= g.M) return;
-            int msg = 0;
-            const int64_t off = map_off(e.mmap, (uint32_t)m, e.seg_on_m ? e.nseg : 1, &msg) + noff;
-            T* out = reinterpret_cast<T*>(pick(e.ptr, e.seg_on_m ? msg : nsg)) + off;
-            const unsigned char* rd = region + rr * PITCH + vc * ES;
-            if constexpr (RESID) {
-                float a[8], b[8];
-                V8<float>::load(reinterpret_cast<const float*>(rd), a);
-                V8<T>::unpack(h, b);
+            hv[p] = u32x4{0u, 0u, 0u, 0u};
+            off[p] = noff + map_off(e.mmap, (uint32_t)m, 1, &d);
+            if (lane_on && rr < 16 && m < g.M)
+                hv[p] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(e.resid) + off[p]);
+        }
 #pragma unroll
-                for (int q = 0; q < 8; ++q) a[q] += b[q];
-                V8<T>::store(out, a);
-            } else {
-                const u32x4 v = *reinterpret_cast<const u32x4*>(rd);
-                if constexpr (ACT != 2) *reinterpret_cast<u32x4*>(out) = v;
-                if constexpr (ACT != 0) {
-                    float a[8], b[8];
-                    V8<T>::unpack(v, a);
-                    V8<T>::unpack(bias_raw, b);
-                    const int64_t ix = (int64_t)m * g.ldc + n;
-                    if constexpr (ACT == 1) {
+        for (int p = 0; p < NPASS; ++p) {
+            const int rr = p * RPI + rr0;
+            if (!lane_on || rr >= 16 || mb + rr >= g.M) continue;
+            float a[8], b[8];
+            V8<float>::load(reinterpret_cast<const float*>(region + rr * PITCH + vc * 4), a);
+            V8<T>::unpack(hv[p], b);
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) a[q] = act_fwd(a[q] + b[q], e.act);
-                        dropout8(e.act_dp, (uint64_t)ix, a);
-                        V8<T>::store(reinterpret_cast<T*>(e.act_out) + ix, a);
-                    } else {
-                        float u[8];
-                        V8<T>::unpack(h, u);
-                        dropout8(e.act_dp, (uint64_t)ix, a);
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            a[q] = to_f(from_f<T>(a[q] * act_grad(u[q] + b[q], e.act)));
-                            cs[q] += a[q];
-                        }
-                        V8<T>::store(out, a);
-                    }
-                }
-            }
-        };
-        if constexpr (ACT == 0) {
-#pragma unroll
-            for (int p = 0; p < NPASS; ++p) pass(p, hv[RESID ? p : 0]);
-        } else {
-            // (not unrolled: the activation code once per 16 rows)
-#pragma unroll 1
-            for (int p = 0; p < NPASS; ++p) {
-                pass(p, hv[0]);
-                if constexpr (ACT == 2) {
-#pragma unroll
-                    for (int t = 0; t + 1 < NPASS; ++t) hv[t] = hv[t + 1];
-                }
-            }
+            for (int q = 0; q < 8; ++q) a[q] += b[q];
+            V8<T>::store(reinterpret_cast<T*>(e.ptr[0]) + off[p], a);
         }
     }
+}
+
+// Outputs in the storage type: the wave's whole tile goes to its own LDS
+// (8-byte writes of four columns; pitch 16 bytes over the row, so 16 rows
+// start on different bank groups) and is read back as 16-byte row pieces in
+// one rolled loop.  ACT 1 / 2: the activation operators of
+// Epilogue::act_mode on each piece (one wave per SIMD has nothing to hide a
+// load behind but its own later pieces: mode 2 keeps the pre-activations of
+// two groups of pieces in flight).
+template <typename T, int FN, int ACT>
+__device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&acc)[8][FN], int mw, int nw,
+                                           unsigned char* region) {
+    constexpr int WN = FN * 16, PITCH = WN * 2 + 16;
+    constexpr int VPR = WN / 8, RPI = 64 / VPR, NP = (128 + RPI - 1) / RPI, U = 4;
+    const int lane = threadIdx.x & 63;
+    const Epilogue& e = g.c;
+    const int rr0 = lane / VPR, vc = (lane % VPR) * 8, n = nw + vc;
+    const bool lane_on = lane < RPI * VPR && n < g.N;
+    const int rows = min(128, g.M - mw);  // rows of the tile inside the output
+    // pre-activations of pieces p .. p + U - 1
+    const T* hp = nullptr;
+    u32x4 h0[ACT == 2 ? U : 1], h1[ACT == 2 ? U : 1];
+    auto request = [&](u32x4 (&h)[ACT == 2 ? U : 1], int p) {
+        if constexpr (ACT == 2) {
+#pragma unroll
+            for (int t = 0; t < U; ++t) {
+                const int rr = (p + t) * RPI + rr0;
+                h[t] = u32x4{0u, 0u, 0u, 0u};
+                if (lane_on && rr < rows) h[t] = *reinterpret_cast<const u32x4*>(hp + (int64_t)(p + t) * RPI * g.ldc);
+            }
+        }
+    };
     if constexpr (ACT == 2) {
-        // lanes with the same 8 columns differ by multiples of VPR
-        static_assert((VPR & (VPR - 1)) == 0, "column groups of a power-of-two lane count");
+        hp = reinterpret_cast<const T*>(e.act_in) + (int64_t)(mw + rr0) * g.ldc + n;
+        request(h0, 0);
+    }
+    u32x4 bias_raw = {0u, 0u, 0u, 0u};
+    if constexpr (ACT != 0)
+        if (lane_on) bias_raw = *reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(e.act_bias) + n);
+    const bool biased = ACT == 0 && e.bias[0] != nullptr;
+    unsigned char* wr = region + (lane & 15) * PITCH + (lane >> 4) * 8;
 #pragma unroll
-        for (int d = VPR; d < 64; d <<= 1)
+    for (int j = 0; j < FN; ++j) {
+        // bias of the lane's four columns (consecutive indices stay inside
+        // one digit: the bias map's lowest radix is a multiple of 8)
+        float bn[4] = {0.f, 0.f, 0.f, 0.f};
+        if (biased) {
+            const int c = nw + j * 16 + 4 * (lane >> 4);
+            int sg = 0;
+            const int64_t bo = map_off(e.bias_map, (uint32_t)(c < g.N ? c : 0), e.bias_nseg, &sg);
+            const T* bp = reinterpret_cast<const T*>(pick(e.bias, sg)) + bo;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], d, 64);
-        if (lane < VPR && n < g.N) V8<float>::store(e.act_part + (int64_t)(mw / 128) * g.N + n, cs);
+            for (int r = 0; r < 4; ++r) bn[r] = to_f(bp[r * e.bias_map.s0]);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            T v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = from_f<T>(ACT == 0 ? acc[i][j][r] + bn[r] : acc[i][j][r]);
+            *reinterpret_cast<u32x2*>(wr + i * 16 * PITCH + j * 32) = __builtin_bit_cast(u32x2, v);
+        }
+    }
+    const unsigned char* rd = region + rr0 * PITCH + vc * 2;
+    if (!g.affine) {
+        // through index maps: the column part of an address is the lane's
+        // for the whole tile, the row part is taken per row
+        int nsg = 0;
+        const int64_t noff = map_off(e.nmap, (uint32_t)(n < g.N ? n : 0), e.seg_on_m ? 1 : e.nseg, &nsg);
+#pragma unroll 4
+        for (int p = 0; p < NP; ++p) {
+            const int rr = p * RPI + rr0;
+            if (!lane_on || rr >= rows) continue;
+            int msg = 0;
+            const int64_t off = map_off(e.mmap, (uint32_t)(mw + rr), e.seg_on_m ? e.nseg : 1, &msg) + noff;
+            *reinterpret_cast<u32x4*>(reinterpret_cast<T*>(pick(e.ptr, e.seg_on_m ? msg : nsg)) + off) =
+                *reinterpret_cast<const u32x4*>(rd + p * RPI * PITCH);
+        }
+        return;
+    }
+    const int64_t ix0 = (int64_t)(mw + rr0) * g.ldc + n;  // element index of piece 0
+    T* out = reinterpret_cast<T*>(e.ptr[0]) + ix0;
+    if constexpr (ACT == 0) {
+#pragma unroll 4
+        for (int p = 0; p < NP; ++p)
+            if (lane_on && p * RPI + rr0 < rows)
+                *reinterpret_cast<u32x4*>(out + (int64_t)p * RPI * g.ldc) =
+                    *reinterpret_cast<const u32x4*>(rd + p * RPI * PITCH);
+    } else {
+        float bb[8], cs[8];
+        V8<T>::unpack(bias_raw, bb);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) cs[q] = 0.f;
+        T* act = ACT == 1 ? reinterpret_cast<T*>(e.act_out) + ix0 : nullptr;
+        auto piece = [&](int p, u32x4 h) {
+            if (!lane_on || p * RPI + rr0 >= rows) return;
+            const int64_t step = (int64_t)p * RPI * g.ldc;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(rd + p * RPI * PITCH);
+            float a[8];
+            V8<T>::unpack(v, a);
+            if constexpr (ACT == 1) {
+                // the stored values, then their activation (the bias +
+                // activation operator's arithmetic)
+                *reinterpret_cast<u32x4*>(out + step) = v;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) a[q] = act_fwd(a[q] + bb[q], e.act);
+                dropout8(e.act_dp, (uint64_t)(ix0 + step), a);
+                V8<T>::store(act + step, a);
+            } else {
+                // the activation backward of the (rounded) gradient
+                float u[8];
+                V8<T>::unpack(h, u);
+                dropout8(e.act_dp, (uint64_t)(ix0 + step), a);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    a[q] = to_f(from_f<T>(a[q] * act_grad(u[q] + bb[q], e.act)));
+                    cs[q] += a[q];
+                }
+                V8<T>::store(out + step, a);
+            }
+        };
+        if constexpr (ACT == 1) {
+#pragma unroll 2
+            for (int p = 0; p < NP; ++p) piece(p, u32x4{0u, 0u, 0u, 0u});
+        } else {
+            static_assert(NP % (2 * U) == 0, "two groups of pieces");
+#pragma unroll 1
+            for (int p = 0; p < NP; p += 2 * U) {
+                request(h1, p + U);
+#pragma unroll
+                for (int t = 0; t < U; ++t) piece(p + t, h0[t]);
+                request(h0, p + 2 * U);  // (past the tile: no rows, no loads)
+#pragma unroll
+                for (int t = 0; t < U; ++t) piece(p + U + t, h1[t]);
+            }
+            // lanes with the same 8 columns differ by multiples of VPR
+            static_assert((VPR & (VPR - 1)) == 0, "column groups of a power-of-two lane count");
+#pragma unroll
+            for (int d = VPR; d < 64; d <<= 1)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], d, 64);
+            if (lane < VPR && n < g.N) V8<float>::store(e.act_part + (int64_t)(mw / 128) * g.N + n, cs);
+        }
     }
 }
 
@@ -533,10 +634,10 @@ __device__ __forceinline__ void wide_block(const GemmArgs& g, unsigned char* sme
     wide_loop<T, BN, AKC, BKC, RSUM>(g, smem, tm, tn, sidx, acc, rs);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int mw = tm * WBM + (w >> 1) * 128, nw = tn * BN + (w & 1) * (BN / 2);
-    unsigned char* region = smem + w * SLOT;
+    static_assert(4 * 128 * (FN * 32 + 16) <= 5 * SLOT && 16 * (FN * 64 + 16) <= SLOT, "staging regions");
     if constexpr (EP == 4) wide_store_f32<FN>(g, acc, mw, nw, sidx);
-    else if constexpr (EP == 3) wide_store<T, FN, 0, true>(g, acc, mw, nw, region);
-    else wide_store<T, FN, EP, false>(g, acc, mw, nw, region);
+    else if constexpr (EP == 3) wide_store_resid<T, FN>(g, acc, mw, nw, smem + w * SLOT);
+    else wide_store<T, FN, EP>(g, acc, mw, nw, smem + w * 128 * (FN * 32 + 16));
 }
 
 template <typename T, int BN, bool AKC, bool BKC, int EP>
@@ -642,12 +743,18 @@ void launch_layout(const GemmArgs& g, int bn, hipStream_t st) {
     else launch_ep<T, 256, false, false>(g, st);
 }
 
-bool operand_ok(const Operand& o) {
-    // (byte offsets of a copy fit 32 bits; 16-byte aligned rows)
+bool operand_ok(const Operand& o, int64_t outer, int64_t K) {
+    // byte offsets of a copy fit 32 bits, rows are 16-byte aligned
     if (o.row.s0 < 0 || o.row.s0 >= (1 << 24) || o.row.s0 % 8 || o.row.s1 % 8 || o.row.s2 % 8) return false;
     for (int i = 0; i < (o.nseg > 0 ? o.nseg : 1); ++i)
         if ((uintptr_t)o.ptr[i] % 16) return false;
-    return o.kcontig ? o.row.r0 % 8 == 0 : o.row.r0 % WK == 0;
+    if (!o.kcontig) return o.row.r0 % WK == 0;  // (64 k-rows: s0 < 2^24)
+    // (the offset of the last row of a segment, in bytes)
+    const uint64_t r0 = o.row.r0, r1 = o.row.r1, n = (uint64_t)outer;
+    const uint64_t d0 = r0 ? std::min(r0, n) : n, d1 = r0 ? (r1 ? std::min(r1, (n + r0 - 1) / r0) : (n + r0 - 1) / r0) : 1;
+    const uint64_t d2 = r0 && r1 && o.nseg <= 1 ? (n + r0 * r1 - 1) / (r0 * r1) : 1;
+    const uint64_t last = (d0 - 1) * o.row.s0 + (d1 - 1) * o.row.s1 + (d2 - 1) * o.row.s2;
+    return o.row.s1 >= 0 && o.row.s2 >= 0 && o.row.r0 % 8 == 0 && (last + K) * 2 < ((uint64_t)1 << 32);
 }
 
 }  // namespace
@@ -657,7 +764,8 @@ bool operand_ok(const Operand& o) {
 // read as zeros).
 bool gemm_wide_ok(const GemmArgs& g, int bn) {
     const Epilogue& e = g.c;
-    if (g.batch != 1 || e.alpha != 1.0f || e.rsum || !operand_ok(g.a) || !operand_ok(g.b)) return false;
+    if (g.batch != 1 || e.alpha != 1.0f || e.rsum || (g.a.kcontig && g.a.nseg > 1) || !operand_ok(g.a, g.M, g.K) ||
+        !operand_ok(g.b, g.N, g.K)) return false;
     if ((g.a.kcontig || g.b.kcontig) && g.K % WK) return false;
     if (bn == 192 && !g.b.kcontig) return false;
     if (g.splits > 1 && (g.kper % WK || (uintptr_t)g.split_ws % 16)) return false;
