@@ -54,80 +54,113 @@ bool lean_ok(const GemmArgs& g, int bks) {
     return true;
 }
 // ------------------------------------------------------------ fp32 path
-// One output element per thread, operands read through the same maps.
-__device__ __forceinline__ float op_elem(const Operand& op, int64_t boff, int outer, int k) {
+// Float32 contractions on v_mfma_f32_16x16x4f32: a 32x32 block tile of four
+// 16x16 waves.  The float32 layers are small (a 64-token layer's largest
+// contraction is 64 x 128 x 128), so what counts is the chain of latencies
+// in one block, not throughput: k goes in steps of 64, whose operands are
+// requested a step ahead as 16-byte pieces along whichever index is
+// contiguous (one map evaluation per piece), so a 128-long contraction waits
+// for memory once; small tiles give more blocks, and 16x16x4 MFMAs a quarter
+// of the serial chain of 32x32x2 ones.  (A 64x64 tile with 16-wide steps
+// gathered element by element took 8-25 us for the contractions of that
+// layer; this kernel 2-4.)
+// LDS holds [outer][k] rows (pitch 68 floats: 16 rows at one 16-byte piece
+// cover all banks once); lane l supplies row l % 16 and, over four MFMAs,
+// k = 16 j + 4 (l / 16) .. + 3: the order of the sum over k is free as
+// long as both operands take the same.  Any map, ragged sizes (zeros past
+// M, N, K); the epilogue stores through the output maps.
+constexpr int F32_T = 32, F32_K = 64, F32_P = F32_K + 4;
+
+// Piece p (of 512) of a 32 x 64 operand step: 4 elements along k of row p /
+// 16 (k-contiguous), or 4 rows of k-row p / 8 (outer-contiguous).
+__device__ __forceinline__ floatx4 f32_piece(const Operand& op, int64_t boff, int p, int o0, int omax, int k0, int kmax) {
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    const int o = op.kcontig ? o0 + (p >> 4) : o0 + (p & 7) * 4;
+    const int k = op.kcontig ? k0 + (p & 15) * 4 : k0 + (p >> 3);
+    if (o >= omax || k >= kmax) return v;
     int seg = 0;
-    if (op.kcontig) {
-        int64_t off = map_off(op.row, (uint32_t)outer, op.nseg, &seg);
-        return reinterpret_cast<const float*>(op.ptr[seg])[boff + off + k];
+    const int64_t off = boff + map_off(op.row, (uint32_t)(op.kcontig ? o : k), op.nseg, &seg) + (op.kcontig ? k : o);
+    const float* src = reinterpret_cast<const float*>(seg_ptr(op.ptr, seg)) + off;
+    const int left = op.kcontig ? kmax - k : omax - o;
+    if (left >= 4 && ((uintptr_t)src & 15u) == 0) return *reinterpret_cast<const floatx4*>(src);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t < left) v[t] = src[t];
+    return v;
+}
+__device__ __forceinline__ void f32_put(float* lds, bool kcontig, int p, floatx4 v) {
+    if (kcontig) {
+        *reinterpret_cast<floatx4*>(lds + (p >> 4) * F32_P + (p & 15) * 4) = v;
+    } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) lds[((p & 7) * 4 + t) * F32_P + (p >> 3)] = v[t];
     }
-    int64_t off = map_off(op.row, (uint32_t)k, op.nseg, &seg);
-    return reinterpret_cast<const float*>(op.ptr[seg])[boff + off + outer];
 }
 
-// Float32 contractions on v_mfma_f32_32x32x2f32: a 64x64 block tile, four
-// waves of 32x32, k-steps of 16 staged through LDS (operands gathered
-// element by element through their index maps, so every layout and ragged
-// size is taken; zeros past M, N, K), fp32 products and accumulation.  Lane
-// l of a 32x32x2 step supplies row l % 32 of A and column l % 32 of B at
-// k = 2 s + l / 32; the result's lane l holds column l % 32 at rows
-// 8 (r / 4) + 4 (l / 32) + r % 4.  The epilogue stores element by element
-// through the output maps (bias, residual, segments as in the 16-bit path).
-constexpr int F32_T = 64, F32_K = 16;
-
 __global__ __launch_bounds__(256) void gemm_f32(GemmArgs g) {
-    __shared__ float sa[F32_K][F32_T + 1];
-    __shared__ float sb[F32_K][F32_T + 1];
+    __shared__ __attribute__((aligned(16))) float sa[F32_T * F32_P];
+    __shared__ __attribute__((aligned(16))) float sb[F32_T * F32_P];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = (blockIdx.y % g.tiles_m) * F32_T, n0 = blockIdx.x * F32_T;
-    const uint32_t z = blockIdx.y / g.tiles_m;
+    const int m0 = (int)(blockIdx.x % g.tiles_m) * F32_T, n0 = (int)(blockIdx.x / g.tiles_m) * F32_T;
+    const uint32_t z = blockIdx.y;
     int dummy = 0;
     const int64_t aoff = map_off(g.a.batch, z, 1, &dummy);
     const int64_t boff = map_off(g.b.batch, z, 1, &dummy);
-    floatx16 acc;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    floatx4 ra[2], rb[2];
+    auto request = [&](int k0) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (int u = 0; u < 2; ++u) {
+            ra[u] = f32_piece(g.a, aoff, u * 256 + tid, m0, g.M, k0, g.K);
+            rb[u] = f32_piece(g.b, boff, u * 256 + tid, n0, g.N, k0, g.K);
+        }
+    };
+    request(0);
     for (int k0 = 0; k0 < g.K; k0 += F32_K) {
-        // each thread gathers 4 elements of each operand tile
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int idx = u * 256 + tid, kk = idx / F32_T, o = idx % F32_T;
-            const int k = k0 + kk;
-            sa[kk][o] = (m0 + o < g.M && k < g.K) ? op_elem(g.a, aoff, m0 + o, k) : 0.f;
-            sb[kk][o] = (n0 + o < g.N && k < g.K) ? op_elem(g.b, boff, n0 + o, k) : 0.f;
+        for (int u = 0; u < 2; ++u) {
+            f32_put(sa, g.a.kcontig, u * 256 + tid, ra[u]);
+            f32_put(sb, g.b.kcontig, u * 256 + tid, rb[u]);
         }
         __syncthreads();
+        if (k0 + F32_K < g.K) request(k0 + F32_K);
+        const float* pa = sa + (wm * 16 + (lane & 15)) * F32_P + (lane >> 4) * 4;
+        const float* pb = sb + (wn * 16 + (lane & 15)) * F32_P + (lane >> 4) * 4;
 #pragma unroll
-        for (int s2 = 0; s2 < F32_K / 2; ++s2) {
-            const int k = 2 * s2 + (lane >> 5);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sa[k][wm * 32 + (lane & 31)], sb[k][wn * 32 + (lane & 31)],
-                                                       acc, 0, 0, 0);
+        for (int j = 0; j < F32_K / 16; ++j) {
+            const floatx4 av = *reinterpret_cast<const floatx4*>(pa + j * 16);
+            const floatx4 bv = *reinterpret_cast<const floatx4*>(pb + j * 16);
+            // (first operand: columns, so that a lane holds 4 consecutive
+            // columns 4 (l / 16) .. + 3 of row l % 16)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[t], av[t], acc, 0, 0, 0);
         }
         __syncthreads();
     }
     const Epilogue& e = g.c;
-    const int n = n0 + wn * 32 + (lane & 31);
-    if (n >= g.N) return;
+    const int m = m0 + wm * 16 + (lane & 15), nb = n0 + wn * 16 + 4 * (lane >> 4);
+    if (m >= g.M) return;
+    int sm = 0;
+    const int64_t moff = map_off(e.batch, z, 1, &dummy) + map_off(e.mmap, (uint32_t)m, e.seg_on_m ? e.nseg : 1, &sm);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (m >= g.M) continue;
+    for (int r = 0; r < 4; ++r) {
+        const int n = nb + r;
+        if (n >= g.N) continue;
         float v = acc[r] * e.alpha;
         if (e.bias[0]) {
             int bseg = 0;
             const int64_t bo = map_off(e.bias_map, (uint32_t)(e.bias_on_m ? m : n), e.bias_nseg, &bseg);
             v += reinterpret_cast<const float*>(seg_ptr(e.bias, bseg))[bo];
         }
-        int sm = 0, sn = 0;
-        const int64_t off = map_off(e.batch, z, 1, &dummy) +
-                            map_off(e.mmap, (uint32_t)m, e.seg_on_m ? e.nseg : 1, &sm) +
-                            map_off(e.nmap, (uint32_t)n, e.seg_on_m ? 1 : e.nseg, &sn);
+        int sn = 0;
+        const int64_t off = moff + map_off(e.nmap, (uint32_t)n, e.seg_on_m ? 1 : e.nseg, &sn);
         const int seg = e.seg_on_m ? sm : sn;
         if (e.resid) v += reinterpret_cast<const float*>(e.resid)[off];
         reinterpret_cast<float*>(seg_ptr(e.ptr, seg))[off] = v;
     }
 }
+
 // Tile configurations: (BM, BN, waves along m, waves along n).
 struct TileCfg {
     int bm, bn, wgm, wgn;
@@ -438,9 +471,9 @@ int launch_gemm(int dtype, const GemmArgs& args, hipStream_t st) {
     if (dtype == G_F32) {
         g.tiles_m = (g.M + F32_T - 1) / F32_T;
         g.tiles_n = (g.N + F32_T - 1) / F32_T;
-        if ((int64_t)g.tiles_m * g.batch > 65535)
+        if ((int64_t)((g.M + 63) / 64) * g.batch > 65535)
             return set_error(DM_ERR_UNSUPPORTED, "fp32 contraction grid too large");
-        dim3 grid(g.tiles_n, g.tiles_m * g.batch);
+        dim3 grid((unsigned)g.tiles_m * g.tiles_n, g.batch);
         hipLaunchKernelGGL(gemm_f32, grid, dim3(256), 0, st, g);
         g.cfg = -1;
         log_launch(g, dtype);
