@@ -93,6 +93,21 @@ template <> struct V8<float> {
     }
 };
 
+// Stores 8 values and leaves in v what was stored: sums of a stored tensor
+// are taken from its own bits (a second conversion of the same product may
+// be fused with the multiplication and round a tie the other way).
+template <typename T>
+__device__ __forceinline__ void store_rounded8(T* p, float v[8]) {
+    u32x4 r = V8<T>::pack(v);
+    asm("" : "+v"(r));
+    *reinterpret_cast<u32x4*>(p) = r;
+    V8<T>::unpack(r, v);
+}
+template <>
+__device__ __forceinline__ void store_rounded8<float>(float* p, float v[8]) {
+    V8<float>::store(p, v);
+}
+
 // ------------------------------------------------------ wave64 reductions
 // Reduction over `width` consecutive lanes (a power of two <= 64); every
 // lane of the group receives the result.  Within a row of 16 lanes the
@@ -235,39 +250,56 @@ __device__ __forceinline__ void keep8(const DropParams& d, uint64_t e0, uint8_t 
 // ----------------------------------------------------------- activations
 enum Act { ACT_GELU = 0, ACT_RELU = 1 };
 
-// erf(x) for x >= 0 and e = exp(-x^2), by the rational approximation of
-// Abramowitz & Stegun, Handbook of Mathematical Functions, 7.1.26:
-// erf(x) = 1 - t (a1 + t (a2 + t (a3 + t (a4 + t a5)))) e, t = 1 / (1 + p x),
-// absolute error <= 1.5e-7.  The exponential is the one the GELU density
-// needs anyway (exp(-u^2 / 2) with x = u / sqrt 2), so GELU and its
-// derivative cost one exp and one reciprocal.
-__device__ __forceinline__ float erf_pos(float x, float e) {
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-    const float poly =
-        t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f),
-                 0.254829592f);
-    return fmaf(-poly, e, 1.0f);
-}
-
-// GELU (exact erf form): Phi(u) = (1 + erf(u / sqrt 2)) / 2
+// The normal distribution's upper tail Q(|u|) = (1 - erf(|u| / sqrt 2)) / 2
+// by the rational approximation of Abramowitz & Stegun, Handbook of
+// Mathematical Functions, 7.1.26 (its halved form, 26.2.17): with
+// t = 1 / (1 + p |u|), Q = t (b1 + t (b2 + t (b3 + t (b4 + t b5)))) e,
+// e = exp(-u^2 / 2), absolute error <= 7.5e-8.  e is the exponential the
+// GELU density needs anyway, so GELU and its derivative cost one exp and one
+// reciprocal; the tail is used as it is for negative u (no cancellation).
 __device__ __forceinline__ float gelu_cdf(float u, float& e) {
-    const float x = u * 0.70710678118654752f;
-    e = __expf(-x * x);
-    const float ea = erf_pos(fabsf(x), e);
-    return 0.5f + 0.5f * (x < 0.0f ? -ea : ea);
+    e = __builtin_amdgcn_exp2f((u * -0.72134752044448170f) * u);  // -log2(e) / 2
+    const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(u), 0.2316419f, 1.0f));
+    const float poly =
+        t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 0.5307027145f, -0.7265760135f), 0.7107068705f), -0.142248368f),
+                 0.127414796f);
+    const float tail = poly * e;
+    return u < 0.0f ? tail : 1.0f - tail;
 }
 
-__device__ __forceinline__ float act_fwd(float u, int act) {
-    if (act == ACT_RELU) return fmaxf(u, 0.0f);
+__device__ __forceinline__ float gelu_fwd(float u) {
     float e;
     return u * gelu_cdf(u, e);
 }
-// d/du of the activation: GELU' = Phi(u) + u * phi(u), phi(u) = exp(-u^2/2) / sqrt(2 pi)
-__device__ __forceinline__ float act_grad(float u, int act) {
-    if (act == ACT_RELU) return u > 0.0f ? 1.0f : 0.0f;
+// d/du GELU(u) = Phi(u) + u * phi(u), phi(u) = exp(-u^2/2) / sqrt(2 pi)
+__device__ __forceinline__ float gelu_grad(float u) {
     float e;
     const float cdf = gelu_cdf(u, e);
     return fmaf(u * 0.39894228040143268f, e, cdf);
+}
+
+// v = act(v + b) and v *= act'(u + b) on 8 elements.  The kind of activation
+// is tested once for the 8 (a test per element, though wave-uniform, left
+// branches between the elements: no two of their serial chains of about 15
+// instructions could overlap, and the Linear-1 epilogue of BERT-large took
+// 16 us more than the plain contraction).
+__device__ __forceinline__ void act_fwd8(float v[8], const float b[8], int act) {
+    if (act == ACT_RELU) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = fmaxf(v[q] + b[q], 0.0f);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = gelu_fwd(v[q] + b[q]);
+    }
+}
+__device__ __forceinline__ void act_grad8(float v[8], const float u[8], const float b[8], int act) {
+    if (act == ACT_RELU) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] *= u[q] + b[q] > 0.0f ? 1.0f : 0.0f;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] *= gelu_grad(u[q] + b[q]);
+    }
 }
 
 }  // namespace dm

@@ -404,12 +404,11 @@ __global__ __launch_bounds__(NT) void act_bwd_k(int64_t rows, int F, const T* __
             if (r + j < r1) {
                 const int64_t off = (r + j) * F + v * 8;
                 dropout8(dp, (uint64_t)off, g[j]);
+                act_grad8(g[j], u[j], bb, act);
+                // (the sums are of the stored values that consumers of dh read)
+                store_rounded8<T>(dh + off, g[j]);
 #pragma unroll
-                for (int q = 0; q < 8; ++q) g[j][q] *= act_grad(u[j][q] + bb[q], act);
-                V8<T>::store(dh + off, g[j]);
-                // sum the stored (rounded) values that consumers of dh read
-#pragma unroll
-                for (int q = 0; q < 8; ++q) acc[q] += to_f(from_f<T>(g[j][q]));
+                for (int q = 0; q < 8; ++q) acc[q] += g[j][q];
             }
     }
     V8<float>::store(part + (int64_t)blockIdx.x * F + v * 8, acc);
@@ -457,9 +456,8 @@ __global__ __launch_bounds__(NT) void act_bwd_t_k(int64_t rows, int F, const T* 
         for (int j = 0; j < 8; ++j) {
             const int64_t off = (r + j) * F + v * 8;
             dropout8(dp, (uint64_t)off, g[j]);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) g[j][q] = to_f(from_f<T>(g[j][q] * act_grad(u[j][q] + bb[q], act)));
-            V8<T>::store(dh + off, g[j]);
+            act_grad8(g[j], u[j], bb, act);
+            store_rounded8<T>(dh + off, g[j]);
 #pragma unroll
             for (int q = 0; q < 8; ++q) acc[q] += g[j][q];
         }
@@ -582,8 +580,7 @@ __global__ __launch_bounds__(NT) void bias_act_fwd_k(int64_t nvec, int cols, con
         float a[8], b[8];
         V8<T>::load(x + r * cols + c, a);
         V8<T>::load(bias + c, b);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) a[q] = act_fwd(a[q] + b[q], act);
+        act_fwd8(a, b, act);
         dropout8(dp, (uint64_t)(r * cols + c), a);
         V8<T>::store(y + r * cols + c, a);
     }

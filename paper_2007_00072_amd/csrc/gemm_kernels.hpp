@@ -1465,8 +1465,7 @@ __device__ __forceinline__ void lean_store_staged(const GemmArgs& g, const LeanO
                             // activation operator's arithmetic, element index
                             // off .. off+7)
                             *reinterpret_cast<u32x4*>(out + off) = v;
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) a[q] = act_fwd(a[q] + b[q], g.c.act);
+                            act_fwd8(a, b, g.c.act);
                             dropout8(g.c.act_dp, (uint64_t)off, a);
                             V8<OutT>::store(reinterpret_cast<OutT*>(g.c.act_out) + o.coff + off, a);
                         } else {
@@ -1475,12 +1474,10 @@ __device__ __forceinline__ void lean_store_staged(const GemmArgs& g, const LeanO
                             float u[8];
                             V8<OutT>::unpack(hcur, u);
                             dropout8(g.c.act_dp, (uint64_t)off, a);
+                            act_grad8(a, u, b, g.c.act);
+                            store_rounded8<OutT>(out + off, a);
 #pragma unroll
-                            for (int q = 0; q < 8; ++q) {
-                                a[q] = to_f(from_f<OutT>(a[q] * act_grad(u[q] + b[q], g.c.act)));
-                                cs[q] += a[q];
-                            }
-                            V8<OutT>::store(out + off, a);
+                            for (int q = 0; q < 8; ++q) cs[q] += a[q];
                         }
                     }
                 }

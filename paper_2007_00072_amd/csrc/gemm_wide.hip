@@ -575,8 +575,7 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&ac
                 // the stored values, then their activation (the bias +
                 // activation operator's arithmetic)
                 *reinterpret_cast<u32x4*>(out + step) = v;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) a[q] = act_fwd(a[q] + bb[q], e.act);
+                act_fwd8(a, bb, e.act);
                 dropout8(e.act_dp, (uint64_t)(ix0 + step), a);
                 V8<T>::store(act + step, a);
             } else {
@@ -584,12 +583,10 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&ac
                 float u[8];
                 V8<T>::unpack(h, u);
                 dropout8(e.act_dp, (uint64_t)(ix0 + step), a);
+                act_grad8(a, u, bb, e.act);
+                store_rounded8<T>(out + step, a);
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    a[q] = to_f(from_f<T>(a[q] * act_grad(u[q] + bb[q], e.act)));
-                    cs[q] += a[q];
-                }
-                V8<T>::store(out + step, a);
+                for (int q = 0; q < 8; ++q) cs[q] += a[q];
             }
         };
         if constexpr (ACT == 1) {
