@@ -188,17 +188,17 @@ struct TileCfg {
 // two and three k-steps ahead); contractions they do not take run as 13
 // would.  25: the ping-pong schedule on a 256x192 tile of 8 waves of 64x96
 // (4 wave rows, 2 columns), for a B operand contiguous along k (otherwise
-// run as 23): 3072-wide outputs get 16 x 16 tiles, every CU one.  26, 27:
-// the wide kernels (gemm_wide.hip), 256x256 and 256x192; the library's own
-// choices only.
+// run as 23): 3072-wide outputs get 16 x 16 tiles, every CU one.  26, 27,
+// 28: the wide kernels (gemm_wide.hip), 256x256, 256x192 and 128x128; the
+// library's own choices only.
 constexpr TileCfg CFGS[] = {{256, 256, 2, 4}, {256, 128, 2, 2}, {128, 128, 2, 2}, {256, 64, 4, 1}, {128, 64, 2, 2},
                             {256, 128, 2, 2}, {128, 128, 2, 2}, {256, 64, 4, 1}, {128, 64, 2, 2},
                             {256, 256, 2, 4}, {256, 128, 2, 2}, {128, 128, 2, 2}, {256, 128, 4, 2},
                             {256, 256, 2, 4}, {256, 256, 2, 4}, {128, 128, 2, 4}, {128, 128, 2, 2},
                             {256, 256, 2, 2}, {128, 128, 2, 2}, {256, 192, 2, 2}, {256, 256, 2, 2}, {256, 192, 2, 2}, {128, 128, 2, 2},
                             {256, 256, 2, 4}, {256, 256, 2, 4}, {256, 192, 4, 2},
-                            {256, 256, 2, 2}, {256, 192, 2, 2}};
-static_assert(sizeof(CFGS) / sizeof(CFGS[0]) == GEMM_CFG_WIDE192 + 1, "configuration table");
+                            {256, 256, 2, 2}, {256, 192, 2, 2}, {128, 128, 2, 2}};
+static_assert(sizeof(CFGS) / sizeof(CFGS[0]) == GEMM_CFG_MID + 1, "configuration table");
 constexpr int NCFG = sizeof(CFGS) / sizeof(CFGS[0]);
 int64_t ntiles(const TileCfg& c, const GemmArgs& g) {
     return (int64_t)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn) * g.batch;
@@ -242,6 +242,9 @@ void choose(GemmArgs& g) {
             g.cfg = 15;
             const int64_t t = ntiles(CFGS[15], g);
             if (split_ok && g.K >= 2048 && t < CUS * 3 / 4) want_split = (int)std::min<int64_t>(4, std::max<int64_t>(1, CUS / t));
+            // the wide kernels' 128x128 tile, from the five 64-wide steps
+            // on that its LDS slots hold
+            if (g.splits <= 1 && g.K >= 512 && gemm_wide_ok(g, 128)) g.cfg = GEMM_CFG_MID;
         }
     }
     // the 32x32x16 kernels' epilogues take no bias along m and only output
@@ -358,6 +361,7 @@ int settle_act(GemmArgs& g, int dtype) {
     // partial rows assume 2 wave rows and its column groups a power-of-two
     // lane count)
     const bool tile_ok = g.cfg == 13 || g.cfg == 15 || g.cfg == 23 || g.cfg == 24 || g.cfg == GEMM_CFG_WIDE ||
+                         g.cfg == GEMM_CFG_MID ||
                          ((g.cfg == 25 || g.cfg == GEMM_CFG_WIDE192) && e.act_mode == 1);
     bool ok = e.act_mode && dtype != G_F32 && tile_ok && !e.rsum && g.splits <= 1 &&
               (g.ep_stage & 1) && !e.out_f32 && !e.bias[0] && e.alpha == 1.0f && e.act_bias && g.batch == 1;

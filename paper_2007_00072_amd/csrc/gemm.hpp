@@ -136,7 +136,7 @@ int gemm_act_parts();
 // Largest tile configuration index a caller may name (contract's tile_cfg,
 // plan entries), and the library's own choices beyond it.
 constexpr int GEMM_MAX_CFG = 25;
-constexpr int GEMM_CFG_WIDE = 26, GEMM_CFG_WIDE192 = 27;
+constexpr int GEMM_CFG_WIDE = 26, GEMM_CFG_WIDE192 = 27, GEMM_CFG_MID = 28;
 
 // Scratch bytes for a split-K contraction.
 inline size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t batch, int splits) {
@@ -158,8 +158,8 @@ int launch_gemm(int dtype, const GemmArgs& args, hipStream_t stream);
 // each, in order.
 int launch_gemm_pair(int dtype, const GemmArgs& a, const GemmArgs& b, hipStream_t stream);
 
-// ---- wide kernels (gemm_wide.hip): 256x256 or 256x192 tiles of four
-// 128x128 (128x96) waves, 64-wide k-steps.
+// ---- wide kernels (gemm_wide.hip): 256x256, 256x192 or 128x128 tiles of
+// four waves, 64-wide k-steps.
 
 // Several contractions run by one grid, tiles dealt out over the XCDs.
 constexpr int GEMM_GROUP_MAX = 5;
@@ -171,7 +171,7 @@ struct GemmGroup {
     int spread;  // 1: every XCD takes an eighth of each contraction's tiles (grids of several rounds);
                  // 0: each XCD takes one contiguous run of all tiles
 };
-// Whether the wide kernel of width bn (256 or 192) takes this contraction.
+// Whether the wide kernel of width bn (256, 192 or 128) takes this contraction.
 bool gemm_wide_ok(const GemmArgs& g, int bn);
 void launch_wide(int dtype, const GemmArgs& g, int bn, hipStream_t st);
 void launch_wide_group(int dtype, const GemmGroup& grp, hipStream_t st);

@@ -181,17 +181,16 @@ struct WideOp<T, R, true, true> {
         return *reinterpret_cast<const u32x4*>(lds + r * 128 + ((c ^ ((r >> 1) & 7)) * 16));
     }
 };
-// outer-contiguous operand, R = 256: LDS keeps [k][outer] rows of 512 bytes,
+// outer-contiguous operand: LDS keeps [k][outer] rows of 2 R bytes,
 // 16-byte chunk c of k-row r at c ^ swz(r); fragments are read with the
 // transposing ds_read_b64_tr_b16 (within 16 lanes, lane i receives element
 // i % 4 of the 8-byte pieces addressed by lanes i / 4 + 4 j), whose eight
-// 4-row groups of two lane groups then fall on different banks.  Copy i of
-// wave w brings k-rows 8 i + 2 w, + 1.  The buffer of a step ends with its
+// 4-row groups of two lane groups then fall on different banks.  The buffer of a step ends with its
 // last valid k-row, and what lies past a buffer's end is read as zeros.
 template <typename T, int R, bool SEG>
 struct WideOp<T, R, false, SEG> {
-    static_assert(R == 256, "k-rows of 32 chunks");
-    static constexpr int NV = 8;
+    static_assert(R == 256 || R == 128, "k-rows of 32 or 16 chunks");
+    static constexpr int CPR = R / 8, KPC = 256 / CPR, NV = WK / KPC;  // chunks a k-row, k-rows a copy
     uint32_t vo[NV];
     int k0, ke, o0;
     uint32_t pitch;  // bytes of a k-row
@@ -203,7 +202,7 @@ struct WideOp<T, R, false, SEG> {
         plain = op.row.r0 == 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int kr = i * 8 + w * 2 + (lane >> 5), c = (lane & 31) ^ swz(kr);
+            const int kr = i * KPC + w * (KPC / 4) + lane / CPR, c = (lane % CPR) ^ swz(kr);
             const int o = o0 + c * 8 < omax ? c * 8 : 0;  // (columns past the end: any valid ones)
             vo[i] = (uint32_t)kr * pitch + (uint32_t)(o * 2);
         }
@@ -405,14 +404,14 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
 
 // Float outputs (split partials, or fp32 C through a row map): 16-byte
 // pieces, four lanes covering 64 contiguous bytes of a row.
-template <int FN>
-__device__ __forceinline__ void wide_store_f32(const GemmArgs& g, const floatx4 (&acc)[8][FN], int mw, int nw,
+template <int FM, int FN>
+__device__ __forceinline__ void wide_store_f32(const GemmArgs& g, const floatx4 (&acc)[FM][FN], int mw, int nw,
                                                int sidx) {
     const int lane = threadIdx.x & 63;
     const int nb = nw + 4 * (lane >> 4);
     const bool part = g.splits > 1;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < FM; ++i) {
         const int m = mw + i * 16 + (lane & 15);
         if (m >= g.M) continue;
         float* row;
@@ -432,8 +431,8 @@ __device__ __forceinline__ void wide_store_f32(const GemmArgs& g, const floatx4 
 // Outputs in the storage type with a residual: 16 rows at a time staged in
 // fp32 through the wave's own LDS (a wave's LDS accesses run in order, so no
 // barrier), read back as row pieces, the residual added before rounding.
-template <typename T, int FN>
-__device__ __forceinline__ void wide_store_resid(const GemmArgs& g, const floatx4 (&acc)[8][FN], int mw, int nw,
+template <typename T, int FM, int FN>
+__device__ __forceinline__ void wide_store_resid(const GemmArgs& g, const floatx4 (&acc)[FM][FN], int mw, int nw,
                                                  unsigned char* region) {
     constexpr int WN = FN * 16, PITCH = WN * 4 + 16;
     constexpr int VPR = WN / 8, RPI = 64 / VPR, NPASS = (16 + RPI - 1) / RPI;
@@ -444,7 +443,7 @@ __device__ __forceinline__ void wide_store_resid(const GemmArgs& g, const floatx
     int d = 0;
     const int64_t noff = map_off(e.nmap, (uint32_t)(n < g.N ? n : 0), 1, &d);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < FM; ++i) {
         const int mb = mw + i * 16;
         if (mb >= g.M) break;
 #pragma unroll
@@ -481,16 +480,16 @@ __device__ __forceinline__ void wide_store_resid(const GemmArgs& g, const floatx
 // Epilogue::act_mode on each piece (one wave per SIMD has nothing to hide a
 // load behind but its own later pieces: mode 2 keeps the pre-activations of
 // two groups of pieces in flight).
-template <typename T, int FN, int ACT>
-__device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&acc)[8][FN], int mw, int nw,
+template <typename T, int FM, int FN, int ACT>
+__device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&acc)[FM][FN], int mw, int nw,
                                            unsigned char* region) {
     constexpr int WN = FN * 16, PITCH = WN * 2 + 16;
-    constexpr int VPR = WN / 8, RPI = 64 / VPR, NP = (128 + RPI - 1) / RPI, U = 4;
+    constexpr int VPR = WN / 8, RPI = 64 / VPR, WM = FM * 16, NP = (WM + RPI - 1) / RPI, U = 4;
     const int lane = threadIdx.x & 63;
     const Epilogue& e = g.c;
     const int rr0 = lane / VPR, vc = (lane % VPR) * 8, n = nw + vc;
     const bool lane_on = lane < RPI * VPR && n < g.N;
-    const int rows = min(128, g.M - mw);  // rows of the tile inside the output
+    const int rows = min(WM, g.M - mw);  // rows of the tile inside the output
     // pre-activations of pieces p .. p + U - 1
     const T* hp = nullptr;
     u32x4 h0[ACT == 2 ? U : 1], h1[ACT == 2 ? U : 1];
@@ -527,7 +526,7 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&ac
             for (int r = 0; r < 4; ++r) bn[r] = to_f(bp[r * e.bias_map.s0]);
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < FM; ++i) {
             T v[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = from_f<T>(ACT == 0 ? acc[i][j][r] + bn[r] : acc[i][j][r]);
@@ -593,7 +592,7 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&ac
 #pragma unroll 2
             for (int p = 0; p < NP; ++p) piece(p, u32x4{0u, 0u, 0u, 0u});
         } else {
-            static_assert(NP % (2 * U) == 0, "two groups of pieces");
+            static_assert(NP % (2 * U) == 0, "whole double groups of pieces");
 #pragma unroll 1
             for (int p = 0; p < NP; p += 2 * U) {
                 request(h1, p + U);
@@ -609,7 +608,7 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&ac
             for (int d = VPR; d < 64; d <<= 1)
 #pragma unroll
                 for (int q = 0; q < 8; ++q) cs[q] += __shfl_xor(cs[q], d, 64);
-            if (lane < VPR && n < g.N) V8<float>::store(e.act_part + (int64_t)(mw / 128) * g.N + n, cs);
+            if (lane < VPR && n < g.N) V8<float>::store(e.act_part + (int64_t)(mw / WM) * g.N + n, cs);
         }
     }
 }
@@ -632,9 +631,9 @@ __device__ __forceinline__ void wide_block(const GemmArgs& g, unsigned char* sme
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int mw = tm * WBM + (w >> 1) * 128, nw = tn * BN + (w & 1) * (BN / 2);
     static_assert(4 * 128 * (FN * 32 + 16) <= 5 * SLOT && 16 * (FN * 64 + 16) <= SLOT, "staging regions");
-    if constexpr (EP == 4) wide_store_f32<FN>(g, acc, mw, nw, sidx);
-    else if constexpr (EP == 3) wide_store_resid<T, FN>(g, acc, mw, nw, smem + w * SLOT);
-    else wide_store<T, FN, EP>(g, acc, mw, nw, smem + w * 128 * (FN * 32 + 16));
+    if constexpr (EP == 4) wide_store_f32<8, FN>(g, acc, mw, nw, sidx);
+    else if constexpr (EP == 3) wide_store_resid<T, 8, FN>(g, acc, mw, nw, smem + w * SLOT);
+    else wide_store<T, 8, FN, EP>(g, acc, mw, nw, smem + w * 128 * (FN * 32 + 16));
 }
 
 template <typename T, int BN, bool AKC, bool BKC, int EP>
@@ -648,6 +647,159 @@ __global__ __launch_bounds__(256) void gemm_wide(GemmArgs g) {
     int tm, tn;
     wide_tile(lid - sidx * nt, g.tiles_m, g.tiles_n, tm, tn);
     wide_block<T, BN, AKC, BKC, false, EP>(g, smem, tm, tn, sidx);
+}
+
+// The same on a 128x128 tile (waves of 64x64), for outputs with too few
+// 256x256 tiles: what bounds it there is the copies (32 KB a step of 512
+// MFMA cycles a wave; copies alone reach about 47 bytes a cycle and CU), so
+// the five 32 KB slots hold whole steps and copies run four steps ahead.
+// The barrier of step s, in its second slice, frees slot s % 5 and publishes
+// step s + 1; step s + 5 is copied into the freed slot, three of its eight
+// copies right after the barrier, the others during the next step's first
+// slice.  (4096 x 1024 x 4096 fp16: the lean 128x128 kernel 45 us.)
+template <typename T, bool AKC, bool BKC, int EP>
+__device__ __forceinline__ void mid_block(const GemmArgs& g, unsigned char* smem, int tm, int tn, int sidx) {
+    constexpr int BT = 128, FM = 4, FN = 4, NM = FM * FN, NR = FM + FN, BP = 4, ST = 5, HALF = SLOT / 2;
+    typedef WideOp<T, BT, AKC, false> OA;
+    typedef WideOp<T, BT, BKC, true> OB;
+    typedef typename WMfma<T>::frag frag;
+    constexpr int NV = OA::NV + OB::NV, EARLY = 3;
+    static_assert(NV == 8 && EARLY * 4 + 1 <= NM - BP + 1 && (NV - EARLY - 1) * 4 + 2 < NM + BP, "schedule");
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = w >> 1, wn = w & 1;
+    const int m0 = tm * BT, n0 = tn * BT;
+    const int kb = sidx * g.kper, ke = min(g.K, kb + g.kper);
+    OA da;
+    OB db;
+    da.init(g.a, kb, ke, m0, g.M, w, lane);
+    db.init(g.b, kb, ke, n0, g.N, w, lane);
+    const uint32_t base = lds_offset(smem) + (uint32_t)w * 1024u;
+    floatx4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int nk = (ke - kb + WK - 1) / WK;
+    frag a[2][FM], b[2][FN];
+    auto read = [&](int buf, const unsigned char* st, int q, int j) {
+        if (j == 0) a[buf][0] = __builtin_bit_cast(frag, OA::frag(st, wm * 64, q, lane));
+        else if (j <= FN) b[buf][j - 1] = __builtin_bit_cast(frag, OB::frag(st + HALF, wn * 64 + (j - 1) * 16, q, lane));
+        else a[buf][j - FN] = __builtin_bit_cast(frag, OA::frag(st, wm * 64 + (j - FN) * 16, q, lane));
+    };
+    auto mma = [&](int buf, int t) { WMfma<T>::run(acc[t / FN][t % FN], b[buf][t % FN], a[buf][t / FN]); };
+    auto ta = da.first(g.a);
+    auto tb = db.first(g.b);
+    auto aim = [&](uint32_t slot, int c) {
+        set_m0(slot, c < OA::NV ? (uint32_t)c * 4096u : (uint32_t)HALF + (uint32_t)(c - OA::NV) * 4096u);
+    };
+    auto copy = [&](int c) {
+        if (c < OA::NV) da.copy(ta, c);
+        else db.copy(tb, c - OA::NV);
+    };
+    // steps 0 .. 3 and the first copies of step 4
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+        if (s < nk) {
+#pragma unroll
+            for (int c = 0; c < (s < ST - 1 ? NV : EARLY); ++c) {
+                aim(base + (uint32_t)s * SLOT, c);
+                asm volatile("s_nop 0" ::: "memory");
+                copy(c);
+            }
+        }
+        if (s < ST - 1) {
+            da.next(g.a, ta);
+            db.next(g.b, tb);
+        }
+    }
+    if (nk >= ST) wait_copies<3 * NV + EARLY>();
+    else wait_copies<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < NR; ++j) read(0, smem, 0, j);
+    asm volatile("s_nop 7" ::: "memory");
+    uint32_t at = 0, last = (ST - 1) * SLOT;  // slots of step s and of step s - 1 (s + 4)
+    auto step = [&](int s, auto old_c, auto new_c) {
+        // OLD: step s + 4 exists (its later copies go out now); NEW: step s + 5
+        constexpr bool OLD = decltype(old_c)::value, NEW = decltype(new_c)::value;
+        const uint32_t nxt = at + SLOT == ST * SLOT ? 0u : at + SLOT;
+        const uint32_t to_old = base + last, to_new = base + at;
+        const unsigned char *S0 = smem + at, *S1 = smem + nxt;
+        // copy c >= EARLY at MFMA 4 (c - EARLY) + 2 of the step
+        auto old_copy = [&](int f) {
+            if (OLD && f % 4 == 1 && f / 4 + EARLY < NV) aim(to_old, f / 4 + EARLY);
+            if (OLD && f % 4 == 2 && f / 4 + EARLY < NV) copy(f / 4 + EARLY);
+        };
+#pragma unroll
+        for (int t = 0; t < NM; ++t) {
+            mma(0, t);
+            if (t < NR) read(1, S0, 1, t);
+            old_copy(t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int t = 0; t < BP; ++t) {
+            mma(1, t);
+            old_copy(NM + t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // step s + 1 has landed; steps s + 2 .. s + 4 may still fly
+        if (OLD) wait_copies<3 * NV>();
+        else if (nk - 2 - s == 2) wait_copies<2 * NV>();
+        else if (nk - 2 - s == 1) wait_copies<NV>();
+        else wait_copies<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (NEW) {
+            da.next(g.a, ta);
+            db.next(g.b, tb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = BP; t < NM; ++t) {
+            mma(1, t);
+            const int u = t - BP;
+            if (u < NR) read(0, S1, 0, u);
+            if (NEW && u % 4 == 0 && u / 4 < EARLY) aim(to_new, u / 4);
+            if (NEW && u % 4 == 1 && u / 4 < EARLY) copy(u / 4);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        last = at;
+        at = nxt;
+    };
+    int s = 0;
+#pragma unroll 1
+    for (; s + ST < nk; ++s) step(s, Flag<true>{}, Flag<true>{});
+    if (s + ST - 1 < nk) {
+        step(s, Flag<true>{}, Flag<false>{});
+        ++s;
+    }
+#pragma unroll 1
+    for (; s < nk; ++s) step(s, Flag<false>{}, Flag<false>{});
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j])::"memory");
+    const int mw = m0 + wm * 64, nw = n0 + wn * 64;
+    if constexpr (EP == 4) wide_store_f32<FM, FN>(g, acc, mw, nw, sidx);
+    else if constexpr (EP == 3) wide_store_resid<T, FM, FN>(g, acc, mw, nw, smem + w * SLOT);
+    else wide_store<T, FM, FN, EP>(g, acc, mw, nw, smem + w * SLOT);
+}
+
+template <typename T, bool AKC, bool BKC, int EP>
+__global__ __launch_bounds__(256) void gemm_mid(GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[5 * SLOT];
+    const int nt = g.tiles_m * g.tiles_n, total = nt * (g.splits > 1 ? g.splits : 1);
+    const int b = (int)blockIdx.x;
+    const int lid = (total & 7) == 0 ? (b & 7) * (total >> 3) + (b >> 3) : b;
+    const int sidx = lid / nt;
+    int tm, tn;
+    wide_tile(lid - sidx * nt, g.tiles_m, g.tiles_n, tm, tn);
+    mid_block<T, AKC, BKC, EP>(g, smem, tm, tn, sidx);
 }
 
 static_assert(offsetof(GemmGroup, g) == 0, "contraction p at p * sizeof(GemmArgs) of the kernel arguments");
@@ -729,9 +881,27 @@ void launch_ep(const GemmArgs& g, hipStream_t st) {
         if (ep == 2) hipLaunchKernelGGL((gemm_wide<T, BN, true, false, 2>), grid, block, 0, st, g);
 }
 
+template <typename T, bool AKC, bool BKC>
+void launch_mid_ep(const GemmArgs& g, hipStream_t st) {
+    const dim3 grid(g.tiles_m * g.tiles_n * (g.splits > 1 ? g.splits : 1)), block(256);
+    const int ep = g.splits > 1 || g.c.out_f32 ? 4 : g.c.act_mode ? g.c.act_mode : g.c.resid ? 3 : 0;
+    if (ep == 4) hipLaunchKernelGGL((gemm_mid<T, AKC, BKC, 4>), grid, block, 0, st, g);
+    else if (ep == 3) hipLaunchKernelGGL((gemm_mid<T, AKC, BKC, 3>), grid, block, 0, st, g);
+    else if (ep == 0) hipLaunchKernelGGL((gemm_mid<T, AKC, BKC, 0>), grid, block, 0, st, g);
+    if constexpr (AKC && BKC)
+        if (ep == 1) hipLaunchKernelGGL((gemm_mid<T, true, true, 1>), grid, block, 0, st, g);
+    if constexpr (AKC && !BKC)
+        if (ep == 2) hipLaunchKernelGGL((gemm_mid<T, true, false, 2>), grid, block, 0, st, g);
+}
+
 template <typename T>
 void launch_layout(const GemmArgs& g, int bn, hipStream_t st) {
-    if (bn == 192) {
+    if (bn == 128) {
+        if (g.a.kcontig && g.b.kcontig) launch_mid_ep<T, true, true>(g, st);
+        else if (g.a.kcontig) launch_mid_ep<T, true, false>(g, st);
+        else if (g.b.kcontig) launch_mid_ep<T, false, true>(g, st);
+        else launch_mid_ep<T, false, false>(g, st);
+    } else if (bn == 192) {
         if (g.a.kcontig) launch_ep<T, 192, true, true>(g, st);
         else launch_ep<T, 192, false, true>(g, st);
     } else if (g.a.kcontig && g.b.kcontig) launch_ep<T, 256, true, true>(g, st);
