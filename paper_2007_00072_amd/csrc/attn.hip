@@ -114,7 +114,7 @@ __host__ __device__ inline int tile_swizzle_mask(int K) {
 }
 
 inline size_t attn_lds_bytes(int K, int es, int nb2) {
-    const size_t s = (size_t)32 * K * es;
+    const size_t s = (size_t)32 * ((K + 31) / 32 * 32) * es;
     if (nb2 == 0) return s;
     const size_t ks = 8 / nb2;
     return std::max(s + (size_t)(NTA / 64) * STG_BYTES, (ks - 1) * nb2 * 4096);
@@ -129,8 +129,10 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
     // dividing K / 8), so the 8-byte tile writes, the 16-byte fragment reads
     // and the row operator's 16-byte accesses spread over the 64 banks as
     // padded rows would, while the tile takes no more than 32 K elements
-    const int K = g.K, J = g.J, swm = tile_swizzle_mask(K);
-    auto at = [&](int r, int col) { return r * K + ((((col >> 3) ^ (r & swm))) << 3) + (col & 7); };
+    // (a key length that is no multiple of 32 pads the tile's rows: the pad
+    // columns' scores are never read, alpha there is zero)
+    const int K = g.K, J = g.J, KP = (K + 31) / 32 * 32, swm = tile_swizzle_mask(KP);
+    auto at = [&](int r, int col) { return r * KP + ((((col >> 3) ^ (r & swm))) << 3) + (col & 7); };
     // Workgroups reach the 8 XCDs round-robin by linear id; the row blocks
     // of one (b, h) are given consecutive ids within one XCD's share, so
     // that XCD's L2 serves the head's key-side rows to all of them
@@ -174,8 +176,10 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
 #pragma unroll
         for (int s = 0; s < DK; ++s) af[s] = *reinterpret_cast<const u32x4*>(arow + 8 * s);
         const T* bbase = reinterpret_cast<const T*>(g.b.ptr) + b * g.b.outer + h * g.b.inner + hh * (g.D / 2);
-        for (int cb = wave; cb < K / 32; cb += NTA / 64) {
-            const T* brow = bbase + (int64_t)(cb * 32 + c) * g.b.ld;
+        // (under a causal mask the keys after the last query are left out)
+        const int ncb = !BWD && g.causal ? min(KP / 32, (j0 + nr + 31) / 32) : KP / 32;
+        for (int cb = wave; cb < ncb; cb += NTA / 64) {
+            const T* brow = bbase + (int64_t)min(cb * 32 + c, K - 1) * g.b.ld;
             u32x4 bf[DK];
 #pragma unroll
             for (int s = 0; s < DK; ++s) bf[s] = *reinterpret_cast<const u32x4*>(brow + 8 * s);
@@ -206,7 +210,7 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
     // s = w / NB2 + KS i.
     constexpr int KS = NB2 > 0 ? 8 / NB2 : 1;
     const int cbn = NB2 > 0 ? wave % NB2 : 0, ks = NB2 > 0 ? wave / NB2 : 0;
-    const int nst = K / 16;
+    const int nst = !BWD && g.causal ? min(KP / 16, (j0 + nr + 15) / 16) : KP / 16;
     const int cnt = (NB2 > 0 && ks < KS) ? (nst - ks + KS - 1) / KS : 0;
     [[maybe_unused]] u32x4 xr[NB2 > 0 ? PF2 : 1];
     [[maybe_unused]] const T* xbase = nullptr;
@@ -214,9 +218,12 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
     auto load_next = [&](int g0) {
 #pragma unroll
         for (int i = 0; i < PF2; ++i)
-            xr[i] = *reinterpret_cast<const u32x4*>(xbase + (int64_t)(16 * min(ks + KS * (g0 + i), nst - 1) +
-                                                                       (lane >> 2)) * g.x.ld);
+            xr[i] = *reinterpret_cast<const u32x4*>(
+                xbase + (int64_t)min(16 * min(ks + KS * (g0 + i), nst - 1) + (lane >> 2), K - 1) * g.x.ld);
     };
+    // rows past the last key are zeros (alpha is zero there, but the row read
+    // in their place may hold an infinity)
+    auto row_in = [&](int i) { return KP == K || 16 * (ks + KS * i) + (lane >> 2) < K; };
     if constexpr (NB2 > 0) {
         xbase = reinterpret_cast<const T*>(g.x.ptr) + b * g.x.outer + h * g.x.inner + cbn * 32 + 8 * (lane & 3);
         if constexpr (!BWD) load_next(0);
@@ -270,10 +277,13 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
                     const u32x4 pp = V8<T>::pack(v[i]);
                     *reinterpret_cast<u32x4*>(reinterpret_cast<T*>(g.out0) + base + col) = pp;
                     V8<T>::unpack(pp, v[i]);
-                    dropout8(g.dp, (uint64_t)(ebase + col), v[i]);
+                    // (keys after the query have probability 0 whatever the mask)
+                    if (!g.causal || col <= j) dropout8(g.dp, (uint64_t)(ebase + col), v[i]);
                     const u32x4 pk = V8<T>::pack(v[i]);
                     if (g.out1) *reinterpret_cast<u32x4*>(reinterpret_cast<T*>(g.out1) + base + col) = pk;
                     if constexpr (NB2 > 0) *reinterpret_cast<u32x4*>(S + at(lr, col)) = pk;
+                } else if (NB2 > 0 && col < KP) {
+                    *reinterpret_cast<u32x4*>(S + at(lr, col)) = u32x4{0u, 0u, 0u, 0u};
                 }
             }
         } else {
@@ -315,7 +325,7 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
     if constexpr (NB2 > 0) {
         if constexpr (BWD) load_next(0);
         __syncthreads();
-        const size_t s_bytes = (size_t)32 * K * sizeof(T);
+        const size_t s_bytes = (size_t)32 * KP * sizeof(T);
         T* stg = reinterpret_cast<T*>(smem_raw + s_bytes + wave * STG_BYTES);
         floatx16 acc;
 #pragma unroll
@@ -328,9 +338,11 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
                 if (g0 + i < cnt) {
                     // the slot's previous reads were issued before these writes, and
                     // one wave's LDS operations complete in order
-                    *reinterpret_cast<u32x4*>(stg + (lane >> 2) * 32 + 8 * (lane & 3)) = xr[i];
+                    const u32x4 zero = {0u, 0u, 0u, 0u};
+                    *reinterpret_cast<u32x4*>(stg + (lane >> 2) * 32 + 8 * (lane & 3)) = row_in(g0 + i) ? xr[i] : zero;
                     if (g0 + i + 1 < cnt)
-                        *reinterpret_cast<u32x4*>(stg + 512 + (lane >> 2) * 32 + 8 * (lane & 3)) = xr[i + 1];
+                        *reinterpret_cast<u32x4*>(stg + 512 + (lane >> 2) * 32 + 8 * (lane & 3)) =
+                            row_in(g0 + i + 1) ? xr[i + 1] : zero;
                     const int s0 = 16 * (ks + KS * (g0 + i));
                     acc = AMfma<T>::run(*reinterpret_cast<const u32x4*>(S + at(c, s0 + 8 * hh)), stage_frag(stg, lane), acc);
                     if (g0 + i + 1 < cnt) {
@@ -377,15 +389,23 @@ void attn_fused_d(const AttnArgs& g, hipStream_t st) {
     const dim3 grid((g.J + 31) / 32, g.B * g.H);
     const int nb2 = g.N2 / 32;
     const size_t lds = attn_lds_bytes(g.K, (int)sizeof(T), nb2);
+    static_assert(NV <= 2 || !BWD, "long rows: forward only");
+    // (more than 64 KB of dynamic LDS has to be asked for)
+    auto launch = [&](auto* kernel) {
+        if (lds > 65536)
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)lds);
+        hipLaunchKernelGGL(kernel, grid, dim3(NTA), lds, st, g);
+    };
     if constexpr (DK == 2 || DK == 4 || DK == 8) {
         switch (nb2) {
-            case 1: hipLaunchKernelGGL((attn_fused_k<T, LPR, NV, DK, BWD, 1>), grid, dim3(NTA), lds, st, g); return;
-            case 2: hipLaunchKernelGGL((attn_fused_k<T, LPR, NV, DK, BWD, 2>), grid, dim3(NTA), lds, st, g); return;
-            case 4: hipLaunchKernelGGL((attn_fused_k<T, LPR, NV, DK, BWD, 4>), grid, dim3(NTA), lds, st, g); return;
+            case 1: launch(attn_fused_k<T, LPR, NV, DK, BWD, 1>); return;
+            case 2: launch(attn_fused_k<T, LPR, NV, DK, BWD, 2>); return;
+            case 4: launch(attn_fused_k<T, LPR, NV, DK, BWD, 4>); return;
             default: break;
         }
     }
-    hipLaunchKernelGGL((attn_fused_k<T, LPR, NV, DK, BWD, 0>), grid, dim3(NTA), lds, st, g);
+    launch(attn_fused_k<T, LPR, NV, DK, BWD, 0>);
 }
 
 // N2 is 0 here unless attn_next_ok admitted it (D and N2 in {32, 64, 128})
@@ -409,7 +429,8 @@ void attn_fused_t(const AttnArgs& g, hipStream_t st) {
     else if (len <= 128) attn_fused_n<T, BWD, 16, 1>(g, st);
     else if (len <= 256) attn_fused_n<T, BWD, 32, 1>(g, st);
     else if (len <= 512) attn_fused_n<T, BWD, 64, 1>(g, st);
-    else attn_fused_n<T, BWD, 64, 2>(g, st);
+    else if (BWD || len <= 1024) attn_fused_n<T, BWD, 64, 2>(g, st);
+    else if constexpr (!BWD) attn_fused_n<T, BWD, 64, 4>(g, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -449,6 +470,7 @@ struct KeysArgs {
     DropParams dp;
     float sm_scale;
     int B, H, J, K, nkb;
+    int causal;         // P is zero for keys after the query: steps before the block's keys are left out
     AttnOp dq, dk, dv;  // outputs (dq written only when nkb == 1)
     float* part;        // nkb > 1: dQ partials [nkb][B*H][J][64]
 };
@@ -536,15 +558,20 @@ __global__ __launch_bounds__(NTA) void attn_bwd_keys_k(KeysArgs g) {
     u32x4 vf[4];
     {
         const int key = k0 + 32 * kg + 16 * ((c32 >> 2) & 1) + 4 * (c32 >> 3) + (c32 & 3);
-        const T* vr = Vz + (int64_t)key * g.v.ld + 32 * hh;
+        // (keys past the end: zero rows, so that d(alpha) is zero there, as P is)
+        const T* vr = Vz + (int64_t)min(key, g.K - 1) * g.v.ld + 32 * hh;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) vf[s] = *reinterpret_cast<const u32x4*>(vr + 8 * s);
+        for (int s = 0; s < 4; ++s) {
+            vf[s] = *reinterpret_cast<const u32x4*>(vr + 8 * s);
+            if (key >= g.K) vf[s] = u32x4{0, 0, 0, 0};
+        }
     }
     // K rows of the block, staged once for the dQ fragments
     for (int pc = tid; pc < KB * 8; pc += NTA) {
         const int r = pc >> 3, c = (pc & 7) * 8;
-        *reinterpret_cast<u32x4*>(lds + OFF_A + hd_off(r, c)) =
-            *reinterpret_cast<const u32x4*>(Kz + (int64_t)(k0 + r) * g.k.ld + c);
+        u32x4 kr = *reinterpret_cast<const u32x4*>(Kz + (int64_t)min(k0 + r, g.K - 1) * g.k.ld + c);
+        if (k0 + r >= g.K) kr = u32x4{0, 0, 0, 0};
+        *reinterpret_cast<u32x4*>(lds + OFF_A + hd_off(r, c)) = kr;
     }
 
     // staging of one step's d(gamma) and Q rows (and D = d(gamma) . gamma):
@@ -582,23 +609,30 @@ __global__ __launch_bounds__(NTA) void attn_bwd_keys_k(KeysArgs g) {
         if (stager && sc == 0) *reinterpret_cast<float*>(lds + OFF_D + 4 * srow) = dd;
     };
     // P of this lane's 16 keys in query row j0 + 32 qg + lane % 32
+    // (the key length is a multiple of 8: each half is wholly inside or past
+    // the end, where P is taken as zero)
     u32x4 pf[2];
+    const int pk0 = k0 + 32 * kg + 16 * hh;
+    const bool pin0 = pk0 < g.K, pin1 = pk0 + 8 < g.K;
+    const int po0 = pin0 ? pk0 : 0, po1 = pin1 ? pk0 + 8 : 0;
     auto p_load = [&](int j0) {
         const int j = min(j0 + 32 * qg + c32, g.J - 1);
-        const T* pr = Pz + (int64_t)j * g.K + k0 + 32 * kg + 16 * hh;
-        pf[0] = *reinterpret_cast<const u32x4*>(pr);
-        pf[1] = *reinterpret_cast<const u32x4*>(pr + 8);
+        const T* pr = Pz + (int64_t)j * g.K;
+        pf[0] = *reinterpret_cast<const u32x4*>(pr + po0);
+        pf[1] = *reinterpret_cast<const u32x4*>(pr + po1);
     };
     const int nit = (g.J + JB - 1) / JB;
-    stage_load(0);
-    p_load(0);
+    const int it0 = g.causal ? k0 / JB : 0;  // (a causal mask has J == K: it0 < nit)
+    static_assert(KB % JB == 0, "whole steps before a key block");
+    stage_load(it0 * JB);
+    p_load(it0 * JB);
     __syncthreads();
     // dQ task: rows of tile qt, columns 32 pt .., keys 64 ch + 16 s + 8 hh + t
     u32x4 kf[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) kf[s] = frag_hd(OFF_A, 64 * ch + 16 * s, 32 * pt);
-    stage_store(0, 0);
-    if (nit > 1) stage_load(JB);
+    stage_store(it0 * JB, it0 & 1);
+    if (it0 + 1 < nit) stage_load((it0 + 1) * JB);
     __syncthreads();
 
     floatx16 accV[2], accK[2];
@@ -614,7 +648,7 @@ __global__ __launch_bounds__(NTA) void attn_bwd_keys_k(KeysArgs g) {
     float* red = reinterpret_cast<float*>(lds + OFF_RED);
     const int kl = 32 * kg + 16 * hh;  // first key (within the block) of this lane's row piece
 
-    for (int it = 0; it < nit; ++it) {
+    for (int it = it0; it < nit; ++it) {
         const int j0 = it * JB;
         const int OFF_DG = OFF_STG + (it & 1) * SB, OFF_Q = OFF_DG + HDT, OFF_D = OFF_Q + HDT;
         // ---- d(alpha)^T: 32 keys x 32 queries
@@ -651,7 +685,7 @@ __global__ __launch_bounds__(NTA) void attn_bwd_keys_k(KeysArgs g) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int r = 4 * q + i;
-                const float pv = valid ? p[r] : 0.f;
+                const float pv = valid && (r < 8 ? pin0 : pin1) ? p[r] : 0.f;
                 const bool keep = !drop || w[q][i] < thr;
                 const float dpv = keep ? da[r] * dscale : 0.f;
                 db[r] = g.sm_scale * pv * (dpv - Dj);
@@ -759,6 +793,7 @@ __global__ __launch_bounds__(NTA) void attn_bwd_keys_k(KeysArgs g) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int key = k0 + 32 * kg + 8 * (r >> 2) + 4 * hh + (r & 3);
+                if (key >= g.K) continue;
                 dvz[(int64_t)key * g.dv.ld + 32 * t + c32] = from_f<T>(accV[t][r]);
                 dkz[(int64_t)key * g.dk.ld + 32 * t + c32] = from_f<T>(accK[t][r]);
             }
@@ -769,7 +804,7 @@ __global__ __launch_bounds__(NTA) void attn_bwd_keys_k(KeysArgs g) {
 // rounded once; thread t handles 8 consecutive head values of one row.
 template <typename T>
 __global__ __launch_bounds__(256) void attn_dq_reduce_k(const float* __restrict__ part, int nkb, int B, int H,
-                                                         int J, AttnOp dq) {
+                                                         int J, int causal_kb, AttnOp dq) {
     const int64_t n = (int64_t)B * H * J * (KV_HD / 8);
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= n) return;
@@ -782,7 +817,9 @@ __global__ __launch_bounds__(256) void attn_dq_reduce_k(const float* __restrict_
     float v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = 0.f;
-    for (int k = 0; k < nkb; ++k) {
+    // under a causal mask (causal_kb keys a block) blocks past the row's query
+    // have no part in it and did not write one
+    for (int k = 0; k < nkb && k * causal_kb <= j; ++k) {
         const floatx4 a = *reinterpret_cast<const floatx4*>(src + k * stride);
         const floatx4 bb = *reinterpret_cast<const floatx4*>(src + k * stride + 4);
 #pragma unroll
@@ -806,32 +843,42 @@ bool attn_fused_ok(int dtype, int K, int D) {
            (D == 16 || D == 32 || D == 48 || D == 64 || D == 96 || D == 128);
 }
 
+bool attn_fwd_ok(int dtype, int K, int D) {
+    // any key length up to 2048: the tile and its staging (32 rows of K
+    // elements and 16 KB) within the 160 KB of LDS
+    return attn_fused_ok(dtype, 32, D) && K % 8 == 0 && K <= 2048;
+}
+
 namespace {
 // key tiles per block: 8 (256 keys) when K allows it and the grid still
 // has about one block per CU, else 4 (128 keys)
+// (the last block of a head may reach past the last key: 256-key blocks
+// only where they pad no more than 128-key ones)
 int keys_kg(int B, int H, int K) {
-    return (K % 256 == 0 && (int64_t)B * H * (K / 256) >= 192) ? 8 : 4;
+    return ((K + 255) / 256 * 256 == (K + 127) / 128 * 128 && (int64_t)B * H * ((K + 255) / 256) >= 192) ? 8 : 4;
 }
+int keys_blocks(int K, int kg) { return (K + 32 * kg - 1) / (32 * kg); }
 AttnOp op_of(const AttnRows& r) { return attn_op(r.ptr, r.outer, r.inner, r.ld); }
 }  // namespace
 
-bool attn_keys_ok(int dtype, int K, int P, int W) {
-    return (dtype == DM_F16 || dtype == DM_BF16) && P == KV_HD && W == KV_HD && K % 128 == 0;
+bool attn_keys_ok(int dtype, int K, int P, int W, int path) {
+    return (path == 0 || (path == 3 && K % 128 == 0)) && (dtype == DM_F16 || dtype == DM_BF16) && P == KV_HD &&
+           W == KV_HD && K % 8 == 0;
 }
 
 size_t attn_keys_part_bytes(int B, int H, int J, int K) {
-    const int nkb = K / (32 * keys_kg(B, H, K));
+    const int nkb = keys_blocks(K, keys_kg(B, H, K));
     return nkb > 1 ? (size_t)nkb * B * H * J * KV_HD * sizeof(float) : 0;
 }
 
 void run_attn_bwd_keys(int dtype, int B, int H, int J, int K, float scaler, AttnRows q, AttnRows k, AttnRows v,
                        AttnRows dgamma, AttnRows gamma, const void* prob, const DropParams& dp, AttnRows dq,
-                       AttnRows dk, AttnRows dv, float* part, hipStream_t st) {
-    const int kg = keys_kg(B, H, K), nkb = K / (32 * kg);
+                       AttnRows dk, AttnRows dv, float* part, hipStream_t st, int causal) {
+    const int kg = keys_kg(B, H, K), nkb = keys_blocks(K, kg);
     KeysArgs g{};
     g.q = op_of(q); g.k = op_of(k); g.v = op_of(v); g.dg = op_of(dgamma); g.gm = op_of(gamma);
     g.prob = prob; g.dp = dp; g.sm_scale = scaler;
-    g.B = B; g.H = H; g.J = J; g.K = K; g.nkb = nkb;
+    g.B = B; g.H = H; g.J = J; g.K = K; g.nkb = nkb; g.causal = causal;
     g.dq = op_of(dq); g.dk = op_of(dk); g.dv = op_of(dv); g.part = part;
     const dim3 grid(nkb, B * H);
     if (dtype == DM_F16) {
@@ -845,17 +892,17 @@ void run_attn_bwd_keys(int dtype, int B, int H, int J, int K, float scaler, Attn
         trace_next("dq_reduce");
         const int64_t n = (int64_t)B * H * J * (KV_HD / 8);
         const dim3 rg((unsigned)((n + 255) / 256));
-        if (dtype == DM_F16) hipLaunchKernelGGL((attn_dq_reduce_k<half_t>), rg, dim3(256), 0, st, part, nkb, B, H, J, g.dq);
-        else hipLaunchKernelGGL((attn_dq_reduce_k<bf16_t>), rg, dim3(256), 0, st, part, nkb, B, H, J, g.dq);
+        if (dtype == DM_F16) hipLaunchKernelGGL((attn_dq_reduce_k<half_t>), rg, dim3(256), 0, st, part, nkb, B, H, J, causal ? 32 * kg : 0, g.dq);
+        else hipLaunchKernelGGL((attn_dq_reduce_k<bf16_t>), rg, dim3(256), 0, st, part, nkb, B, H, J, causal ? 32 * kg : 0, g.dq);
     }
 }
 
 bool attn_next_ok(int dtype, int K, int D, const AttnNext& n) {
     const int es = 2;
-    return attn_fused_ok(dtype, K, D) && (D == 32 || D == 64 || D == 128) &&
+    return attn_fwd_ok(dtype, K, D) && (D == 32 || D == 64 || D == 128) &&
            (n.N == 32 || n.N == 64 || n.N == 128) && n.x && n.out &&
            reinterpret_cast<uintptr_t>(n.x) % 16 == 0 && n.x_outer % 8 == 0 && n.x_inner % 8 == 0 &&
-           n.x_ld % 8 == 0 && n.x_ld >= n.N && attn_lds_bytes(K, es, n.N / 32) <= 65536;
+           n.x_ld % 8 == 0 && n.x_ld >= n.N && attn_lds_bytes(K, es, n.N / 32) <= 160 * 1024;
 }
 
 namespace {

@@ -105,16 +105,18 @@ void run_bdrln_fwd(int dtype, int64_t rows, int cols, const void* x, const void*
 // Attention scores without the score tensor in HBM (attn.hip).  Operand
 // element (z = b*H + h, row r, contraction index d) sits at
 // ptr + b*outer + h*inner + r*ld + d; P, alpha and d(beta) are [B][H][J][K].
-// attn_fused_ok: dtype fp16 / bf16, K a multiple of 32 up to 960, D (the
-// contraction length) in {16, 32, 48, 64, 96, 128}.
+// attn_fused_ok (backward, row form): dtype fp16 / bf16, K a multiple of 32
+// up to 960, D (the contraction length) in {16, 32, 48, 64, 96, 128};
+// attn_fwd_ok (forward): K any multiple of 8 up to 2048.
 bool attn_fused_ok(int dtype, int K, int D);
+bool attn_fwd_ok(int dtype, int K, int D);
 // The contraction that follows in the same launch: out[z][j][n] =
 // sum_k tile[z][j][k] x[z][k][n] with x element (z, k, n) at
 // x + b*x_outer + h*x_inner + k*x_ld + n and out element (z, j, n) at
 // out + b*o_outer + h*o_inner + j*o_ld + n; n < N.  attn_next_ok: the
 // scores' own conditions, D (the first contraction's length) and N in
 // {32, 64, 128}, x 16-byte aligned with strides that are multiples of 8
-// elements, and the block's LDS within 64 KB.
+// elements, and the block's LDS within 160 KB.
 struct AttnNext {
     const void* x = nullptr;
     int64_t x_outer = 0, x_inner = 0, x_ld = 0;
@@ -143,17 +145,20 @@ void run_attn_scores_bwd(int dtype, int B, int H, int J, int K, int D, float sca
 // d(alpha), alpha or d(beta).
 // Row operands as for the score kernels: element (z = b*H + h, row r, d) at
 // ptr + b*outer + h*inner + r*ld + d.  attn_keys_ok: fp16 / bf16, P = W =
-// 64, K a multiple of 128 (all rows 16-byte aligned).  part: fp32 scratch of
+// 64, K a multiple of 8 (all rows 16-byte aligned), for the launch grouping
+// `path` of the plan (3, scores and the next contraction together: K a
+// multiple of 128, the row form otherwise).  causal: P is zero for keys
+// after the query.  part: fp32 scratch of
 // attn_keys_part_bytes (nullptr allowed when that is 0).
 struct AttnRows {
     const void* ptr;
     int64_t outer, inner, ld;
 };
-bool attn_keys_ok(int dtype, int K, int P, int W);
+bool attn_keys_ok(int dtype, int K, int P, int W, int path);
 size_t attn_keys_part_bytes(int B, int H, int J, int K);
 void run_attn_bwd_keys(int dtype, int B, int H, int J, int K, float scaler, AttnRows q, AttnRows k, AttnRows v,
                        AttnRows dgamma, AttnRows gamma, const void* prob, const DropParams& dp, AttnRows dq,
-                       AttnRows dk, AttnRows dv, float* part, hipStream_t st);
+                       AttnRows dk, AttnRows dv, float* part, hipStream_t st, int causal);
 // alpha = dropout(P) from the stored probabilities [B][H][J][K] (K % 8 == 0)
 void run_alpha_from_prob(int dtype, int B, int H, int J, int K, const void* prob, const DropParams& dp, void* alpha,
                          hipStream_t st);

@@ -107,7 +107,7 @@ void plan_attention(const Dims& x, int mode, Carver& sv, Carver& fw, Carver& bw,
     }
     p.prob = sv.take(es * x.S);
     p.gamma = sv.take(es * x.Tq * x.H * x.W);
-    p.gamma32 = attn_keys_ok(x.dtype, (int)x.K, (int)x.P, (int)x.W) ? sv.take(4 * x.Tq * x.H * x.W) : 0;
+    p.gamma32 = attn_keys_ok(x.dtype, (int)x.K, (int)x.P, (int)x.W, 0) ? sv.take(4 * x.Tq * x.H * x.W) : 0;
     p.beta = fw.take(es * x.S);
     p.alpha_f = fw.take(es * x.S);
     p.dgamma = bw.take(es * x.Tq * x.H * x.W);
@@ -387,7 +387,7 @@ int attention_core_fwd(const Dims& x, float scaler, const DropParams& dp, const 
                        hipStream_t st) {
     const int64_t Z = x.B * x.H, J = x.J, K = x.K, P = x.P, W = x.W, HW = x.H * x.W;
     const int path = current_attn_path();
-    if (path != 1 && attn_fused_ok(x.dtype, (int)K, (int)P)) {
+    if (path != 1 && attn_fwd_ok(x.dtype, (int)K, (int)P)) {
         // QK^T and the softmax + dropout in one launch (beta stays on chip),
         // and Gamma in the same launch when its shape allows
         AttnNext nx;
@@ -479,7 +479,7 @@ int attention_core_bwd(const Dims& x, float scaler, const DropParams& dp, const 
     }
     const IdxMap zg = make_map((uint32_t)H, 0, W, J * HW, 0);  // z=(b,h) -> gamma-like token-major offset
     const int path = current_attn_path();
-    if ((path == 0 || path == 3) && gamma32 && attn_keys_ok(x.dtype, (int)K, (int)P, (int)W)) {
+    if (gamma32 && attn_keys_ok(x.dtype, (int)K, (int)P, (int)W, path)) {
         // Gamma dX1, the softmax + dropout backward, Gamma dX2 and both QK^T
         // gradients in one launch over key blocks, reading P once (dQ
         // partial sums of several key blocks added by a second launch)
@@ -488,7 +488,7 @@ int attention_core_bwd(const Dims& x, float scaler, const DropParams& dp, const 
                           AttnRows{k, H * K * P, K * P, P}, AttnRows{v, H * K * W, K * W, W},
                           AttnRows{dgamma, J * HW, W, HW}, AttnRows{gamma32, J * HW, W, HW}, prob, dp,
                           AttnRows{dq, J * ldq, P, ldq}, AttnRows{dk, K * ldk, P, ldk}, AttnRows{dv, K * ldv, W, ldv},
-                          reinterpret_cast<float*>(dalpha), st);
+                          reinterpret_cast<float*>(dalpha), st, x.causal);
         return check_launch("attention key-block backward");
     }
     {
@@ -500,7 +500,7 @@ int attention_core_bwd(const Dims& x, float scaler, const DropParams& dp, const 
     AttnNext nq;
     nq.x = k; nq.x_outer = H * K * P; nq.x_inner = K * P; nq.x_ld = P;
     nq.out = dq; nq.o_outer = J * ldq; nq.o_inner = P; nq.o_ld = ldq; nq.N = (int)P;
-    const bool with_dq = fused && path != 2 && attn_next_ok(x.dtype, (int)K, (int)W, nq);
+    const bool with_dq = fused && path != 2 && (int)K <= 768 && attn_next_ok(x.dtype, (int)K, (int)W, nq);
     if (fused) {
         // Gamma dX1 and the scaled softmax + dropout backward in one launch
         // (dalpha stays on chip): dbeta[z][j][k]; QK^T dX1 in the same
@@ -678,7 +678,7 @@ int attn_backward_form(const dm_layer_desc* d, int32_t* key_blocks) {
     if (!key_blocks) return set_error(DM_ERR_ARG, "key_blocks is NULL");
     PlanScope plan_(d->plan);
     const int path = current_attn_path();
-    *key_blocks = (path == 0 || path == 3) && attn_keys_ok(d->dtype, d->K, d->P, d->W);
+    *key_blocks = attn_keys_ok(d->dtype, d->K, d->P, d->W, path);
     return DM_OK;
 }
 

@@ -1,0 +1,45 @@
+"""Attention at key lengths that are no multiple of the kernels' tiles: the
+forward's padded score tile (32 keys), the key-block backward's last block
+(128 or 256 keys), rows longer than 1024 keys, causal masks that leave out
+whole key tiles and query steps, and one key tile in all."""
+import pytest
+import torch
+
+from paper_2007_00072_amd import lib
+from paper_2007_00072_amd.inputs import WORKLOADS, Shape
+from test_gpu_layer import check_encoder, check_mha, run_encoder, small
+from test_gpu_plan import _launches
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name", ["bert_large_f16", "bert_base_bf16"])
+@pytest.mark.parametrize("J,causal", [(8, False), (40, False), (136, False), (200, True), (264, False), (392, True)])
+def test_encoder_key_lengths(name, J, causal):
+    wl = small(name, B=2, J=J, K=J, H=4, P=64, W=64, I=256, F=512).with_(p_attn=0.1)
+    _, labels = _launches(wl, None)
+    assert "F2-4 qkt_softmax_gamma" in labels and "B13-17 score_bwd_keys" in labels, labels
+    check_encoder(wl, layer=1, causal=causal)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("J,K", [(72, 24), (24, 136), (40, 776), (16, 1032), (32, 1096)])
+def test_mha_key_lengths(dtype, J, K):
+    # cross attention; 776 to 1096 keys: tiles above 64 KB of LDS, rows of
+    # two and four 8-element vectors per lane
+    wl = WORKLOADS["mha_large_f16"].with_(shape=Shape(B=2, J=J, K=K, H=2, P=64, W=64, I=128), dtype=dtype, layout="bji",
+                                          p_attn=0.1)
+    check_mha(wl, self_attention=False)
+
+
+def test_key_padding_leaves_neighbours_alone():
+    # 256-key blocks with the last one padded (240 blocks of one head each),
+    # against the row form of the same backward
+    wl = small("bert_large_f16", B=24, J=248, K=248, H=8, P=64, W=64, I=512, F=512).with_(p_attn=0.1)
+    L0, _, _, _, y0, dx0 = run_encoder(wl)
+    L1, _, _, _, y1, dx1 = run_encoder(wl, plan=lib.Plan((), attn_path=1))
+    assert lib.attn_backward_form(L0.desc) and not lib.attn_backward_form(L1.desc)
+    # the two forms round d(alpha) and P's products at different places
+    assert (dx0.float() - dx1.float()).norm() <= 3e-3 * dx1.float().norm()
+    for n in ("wq", "wk", "wv"):
+        assert (L0.grads[n] - L1.grads[n]).norm() <= 3e-3 * L1.grads[n].norm(), n
