@@ -140,7 +140,9 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
     const int nrb = (int)gridDim.x, nblocks = nrb * (int)gridDim.y;
     int lid = (int)blockIdx.y * nrb + (int)blockIdx.x;
     if ((nblocks & 7) == 0) lid = (lid & 7) * (nblocks >> 3) + (lid >> 3);
-    const int z = lid / nrb, j0 = (lid - z * nrb) * 32;
+    // (under a causal mask the rows with most keys go first, so that the
+    // launch does not end with them)
+    const int z = lid / nrb, rb = lid - z * nrb, j0 = (!BWD && g.causal ? nrb - 1 - rb : rb) * 32;
     const int b = z / g.H, h = z - b * g.H;
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
                 const int col = (gl + i * LPR) * 8;
-                if (active && col < K) {
+                if (active && col < K && !(g.causal && col > j)) {
                     V8<T>::unpack(*reinterpret_cast<const u32x4*>(S + at(lr, col)), v[i]);
                     if (g.causal) {
 #pragma unroll
@@ -261,9 +263,16 @@ __global__ __launch_bounds__(NTA) void attn_fused_k(AttnArgs g) {
             float sum = 0.f;
             const ExpShift ex(mx);
 #pragma unroll
-            for (int i = 0; i < NV; ++i)
+            for (int i = 0; i < NV; ++i) {
+                // (a piece past the query is zero without its exponentials)
+                if (g.causal && (gl + i * LPR) * 8 > j) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) v[i][q] = 0.f;
+                    continue;
+                }
 #pragma unroll
                 for (int q = 0; q < 8; ++q) { v[i][q] = ex(v[i][q]); sum += v[i][q]; }
+            }
             sum = group_sum<LPR>(sum);
             if (!active) continue;
             const float rinv = __builtin_amdgcn_rcpf(sum);
@@ -525,7 +534,15 @@ __global__ __launch_bounds__(NTA) void attn_bwd_keys_k(KeysArgs g) {
     int lid = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
     // the key blocks of one head run on one XCD (see attn_fused_k)
     if ((nblk & 7) == 0) lid = (lid & 7) * (nblk >> 3) + (lid >> 3);
-    const int z = lid / g.nkb, kb = lid - z * g.nkb;
+    int z = lid / g.nkb, kb = lid - z * g.nkb;
+    if (g.causal) {
+        // the first key blocks walk the most queries: all heads' first, then
+        // their second ones, ... (each XCD its own heads where they divide)
+        const int nx = (nblk & 7) == 0 && (nz & 7) == 0 ? 8 : 1, per = nblk / nx, hp = nz / nx;
+        const int x = lid / per, i = lid - x * per;
+        kb = i / hp;
+        z = x * hp + i - kb * hp;
+    }
     const int b = z / g.H, h = z - b * g.H;
     const int k0 = kb * KB;
     const int tid = threadIdx.x, lane = tid & 63, c32 = lane & 31, hh = lane >> 5;
@@ -854,7 +871,11 @@ namespace {
 // has about one block per CU, else 4 (128 keys)
 // (the last block of a head may reach past the last key: 256-key blocks
 // only where they pad no more than 128-key ones)
-int keys_kg(int B, int H, int K) {
+// (a causal mask leaves the blocks of one head unequal work: 128-key blocks,
+// two rounds of them filling up to the same length: 4 x 1024 tokens, 64
+// heads, 92 us with 256-key blocks)
+int keys_kg(int B, int H, int K, int causal) {
+    if (causal && K > 256) return 4;
     return ((K + 255) / 256 * 256 == (K + 127) / 128 * 128 && (int64_t)B * H * ((K + 255) / 256) >= 192) ? 8 : 4;
 }
 int keys_blocks(int K, int kg) { return (K + 32 * kg - 1) / (32 * kg); }
@@ -866,15 +887,15 @@ bool attn_keys_ok(int dtype, int K, int P, int W, int path) {
            W == KV_HD && K % 8 == 0;
 }
 
-size_t attn_keys_part_bytes(int B, int H, int J, int K) {
-    const int nkb = keys_blocks(K, keys_kg(B, H, K));
+size_t attn_keys_part_bytes(int B, int H, int J, int K, int causal) {
+    const int nkb = keys_blocks(K, keys_kg(B, H, K, causal));
     return nkb > 1 ? (size_t)nkb * B * H * J * KV_HD * sizeof(float) : 0;
 }
 
 void run_attn_bwd_keys(int dtype, int B, int H, int J, int K, float scaler, AttnRows q, AttnRows k, AttnRows v,
                        AttnRows dgamma, AttnRows gamma, const void* prob, const DropParams& dp, AttnRows dq,
                        AttnRows dk, AttnRows dv, float* part, hipStream_t st, int causal) {
-    const int kg = keys_kg(B, H, K), nkb = keys_blocks(K, kg);
+    const int kg = keys_kg(B, H, K, causal), nkb = keys_blocks(K, kg);
     KeysArgs g{};
     g.q = op_of(q); g.k = op_of(k); g.v = op_of(v); g.dg = op_of(dgamma); g.gm = op_of(gamma);
     g.prob = prob; g.dp = dp; g.sm_scale = scaler;

@@ -250,7 +250,7 @@ void choose(GemmArgs& g) {
     // the 32x32x16 kernels' epilogues take no bias along m and only output
     // maps affine over 32-wide blocks; of them only the lean 128x128 kernel
     // takes a residual operand
-    if (((g.c.bias[0] && g.c.bias_on_m) || !g.blk32) && g.cfg >= 9) g.cfg = 8;
+    if (((g.c.bias[0] && g.c.bias_on_m) || !g.blk32) && g.cfg >= 9 && g.cfg < GEMM_CFG_WIDE) g.cfg = 8;
     if (g.c.resid && g.cfg >= 9 && g.cfg < GEMM_CFG_WIDE && g.cfg != 15 && g.cfg != 16 && g.cfg != 18 && g.cfg != 22) g.cfg = 8;
     if (g.splits <= 0) {
         int s = split_ok ? want_split : 1;
@@ -383,23 +383,24 @@ thread_local int t_act_parts = 0;
 thread_local int t_rsum_parts = 0;
 
 // Keeps the row-sum request only where the kernel that runs produces it
-// (the lean 256x256 and 128x128 tiles, both 4 wave tiles wide, unsplit, A
-// outer-contiguous) and its partial rows fit.
+// (the lean 256x256 and 128x128 tiles, both 4 wave tiles wide, and the wide
+// 128x128 one, unsplit, A outer-contiguous) and its partial rows fit.
 void settle_rowsums(GemmArgs& g) {
-    constexpr int WGN = 4;
-    const bool lean1 = g.cfg == 13 || g.cfg == 15;
-    const int nw = g.tiles_n * WGN;
-    const bool ok = g.c.rsum != nullptr && lean1 && g.splits <= 1 && !g.a.kcontig && g.batch == 1 &&
+    // (partial rows: one per wave along n and tile column)
+    const int nw = g.tiles_n * (g.cfg == GEMM_CFG_MID ? 2 : 4);
+    const bool ok = g.c.rsum != nullptr && (g.cfg == 13 || g.cfg == 15 || g.cfg == GEMM_CFG_MID) && g.splits <= 1 && !g.a.kcontig && g.batch == 1 &&
                     nw <= g.c.rsum_cap && g.c.rsum_ld >= g.M;
     t_rsum_parts = ok ? nw : 0;
     if (!ok) g.c.rsum = nullptr;
 }
 
-void log_launch(const GemmArgs& g, int dtype) {
+// x: the contraction as asked for (g may run its transpose)
+void log_launch(const GemmArgs& g, int dtype, const GemmArgs* x = nullptr) {
     if (!t_log_on) return;
+    if (!x) x = &g;
     dm_contract_choice r{};
-    r.M = g.M; r.N = g.N; r.K = g.K; r.batch = g.batch; r.dtype = dtype;
-    r.a_kcontig = g.a.kcontig ? 1 : 0; r.b_kcontig = g.b.kcontig ? 1 : 0;
+    r.M = x->M; r.N = x->N; r.K = x->K; r.batch = x->batch; r.dtype = dtype;
+    r.a_kcontig = x->a.kcontig ? 1 : 0; r.b_kcontig = x->b.kcontig ? 1 : 0;
     r.tile_cfg = g.cfg; r.splits = g.splits > 1 ? g.splits : 1;
     strncpy(r.label, trace_current_label(), sizeof(r.label) - 1);
     t_log.push_back(r);
@@ -448,6 +449,20 @@ int plan_log_copy(dm_contract_choice* out, int cap) {
 // Validation, plan and configuration of a 16-bit contraction; `pair`: when
 // no plan entry fixes the configuration, ask for the lean 128x128 kernel
 // unsplit (what a paired launch runs).
+// The same contraction with its outputs transposed (C^T = B^T A^T): the
+// operands and the output indexes trade places.
+static GemmArgs transposed(const GemmArgs& x) {
+    GemmArgs g = x;
+    std::swap(g.M, g.N);
+    std::swap(g.a, g.b);
+    Epilogue& e = g.c;
+    std::swap(e.mmap, e.nmap);
+    e.contig_n = !e.contig_n;
+    e.seg_on_m = e.nseg > 1 ? !e.seg_on_m : e.seg_on_m;
+    e.bias_on_m = e.bias[0] ? !e.bias_on_m : e.bias_on_m;
+    return g;
+}
+
 static int prepare(GemmArgs& g, int dtype, bool pair) {
     if (g.K % 8 || g.M % 8 || g.N % 8)
         return set_error(DM_ERR_UNSUPPORTED, "contraction sizes must be multiples of 8");
@@ -457,6 +472,14 @@ static int prepare(GemmArgs& g, int dtype, bool pair) {
     set_affine(g);
     set_ep_stage(g);
     if (g.cfg < 0) apply_plan(g, dtype);
+    // an output contiguous along m (the paper's [i][b][j] order) as its
+    // transpose, where the wide kernels then take it: they store along n
+    if (g.cfg < 0 && !pair && !g.c.contig_n && !g.c.rsum && !g.c.act_mode && g.batch == 1 && g.K >= 512 && g.M > 64) {
+        GemmArgs t = transposed(g);
+        set_affine(t);
+        set_ep_stage(t);
+        if (gemm_wide_ok(t, 128)) g = t;
+    }
     if (pair && g.cfg < 0) { g.cfg = 15; g.splits = 1; }
     choose(g);
     if (g.splits > 1 && (int64_t)g.splits * g.batch * g.M * g.N > g.split_cap)
@@ -494,7 +517,7 @@ int launch_gemm(int dtype, const GemmArgs& args, hipStream_t st) {
             }
         } else if (dtype == G_F16) launch_tiles_f16(g, st);
         else launch_tiles_bf16(g, st);
-        log_launch(g, dtype);
+        log_launch(g, dtype, &args);
     }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(DM_ERR_DEVICE, "contraction launch: %s", hipGetErrorString(err));

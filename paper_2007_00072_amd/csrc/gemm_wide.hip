@@ -238,14 +238,61 @@ struct WideOp<T, R, false, SEG> {
 
 template <bool V> struct Flag { static constexpr bool value = V; };
 
+// RSUM (A outer-contiguous): partial sums of A's rows over k, for
+// Epilogue::rsum.  The 2 tiles_n waves that read the same rows share the
+// 32-wide slices u = 0, 1, .. round robin; a wave whose turn it is adds its
+// A fragments up with MFMAs against ones.
+template <typename T, int FM, bool RSUM>
+struct RowSums {
+    typedef typename WMfma<T>::frag frag;
+    floatx4 rs[RSUM ? FM : 1];
+    frag ones;
+    int next, stride;
+    bool on;
+    __device__ __forceinline__ RowSums(const GemmArgs& g, int tn, int wn) {
+        if constexpr (RSUM) {
+            on = g.c.rsum != nullptr;
+            stride = g.tiles_n * 2;
+            next = tn * 2 + wn;
+#pragma unroll
+            for (int i = 0; i < FM; ++i) rs[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+            // (kept in registers: formed again next to an MFMA it would need
+            // wait states that the compiler does not insert before assembly)
+            ones = WMfma<T>::ones();
+            asm volatile("" : "+v"(ones));
+        }
+    }
+    __device__ __forceinline__ void add(const frag (&a)[FM], int u) {
+        if constexpr (RSUM) {
+            if (on && u == next) {
+                asm volatile("s_nop 3" ::: "memory");
+#pragma unroll
+                for (int i = 0; i < FM; ++i) rowsum_mfma(rs[i], ones, a[i]);
+                next += stride;
+            }
+        }
+    }
+    // after the k-loop's last MFMAs have settled
+    __device__ __forceinline__ void store(const GemmArgs& g, int mw, int sidx, int tn, int wn, int lane) {
+        if constexpr (RSUM) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i) asm volatile("" : "+v"(rs[i])::"memory");
+            if (!on) return;
+            float* prow = g.c.rsum + (int64_t)(sidx * stride + tn * 2 + wn) * g.c.rsum_ld;
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+                const int m = mw + i * 16 + lane;
+                if (lane < 16 && m < g.M) prow[m] = rs[i][0];
+            }
+        }
+    }
+};
+
 // The k-loop of one block tile: acc[i][j] of lane l = element (row
 // 16 i + l % 16, columns 16 j + 4 (l / 16) .. + 3) of the wave's tile.
-// RSUM (A outer-contiguous): also partial sums of A's rows over k, for
-// Epilogue::rsum; the 2 tiles_n waves that read the same rows share the
-// 32-wide slices round robin.
 template <typename T, int BN, bool AKC, bool BKC, bool RSUM>
 __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem, int tm, int tn, int sidx,
-                                          floatx4 (&acc)[8][BN / 32], floatx4 (&rs)[RSUM ? 8 : 1]) {
+                                          floatx4 (&acc)[8][BN / 32]) {
     constexpr int FM = 8, FN = BN / 32, NM = FM * FN, NR = FM + FN;
     typedef WideOp<T, WBM, AKC, false> OA;
     typedef WideOp<T, BN, BKC, true> OB;
@@ -270,17 +317,7 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const bool rsum = RSUM && g.c.rsum != nullptr;
-    const int rs_nw = g.tiles_n * 2;
-    int rs_next = tn * 2 + wn;
-    if constexpr (RSUM) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) rs[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    // (kept in registers: formed again next to an MFMA it would need wait
-    // states that the compiler does not insert before assembly)
-    frag ones = WMfma<T>::ones();
-    if constexpr (RSUM) asm volatile("" : "+v"(ones));
+    RowSums<T, FM, RSUM> rs(g, tn, wn);
 
     const int nk = (ke - kb + WK - 1) / WK;
     frag a[2][FM], b[2][FN];
@@ -291,16 +328,6 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
         else a[buf][j - FN] = __builtin_bit_cast(frag, OA::frag(A, wm * 128 + (j - FN) * 16, q, lane));
     };
     auto mma = [&](int buf, int t) { WMfma<T>::run(acc[t / FN][t % FN], b[buf][t % FN], a[buf][t / FN]); };
-    auto row_sums = [&](int buf, int u) {
-        if constexpr (RSUM) {
-            if (rsum && u == rs_next) {
-                asm volatile("s_nop 3" ::: "memory");
-#pragma unroll
-                for (int i = 0; i < FM; ++i) rowsum_mfma(rs[i], ones, a[buf][i]);
-                rs_next += rs_nw;
-            }
-        }
-    };
     // steps 0 and 1 (slots 0..3)
     auto ta = da.first(g.a);
     auto tb = db.first(g.b);
@@ -346,7 +373,7 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
             if (MORE && t % CA == 2 && t / CA < OA::NV) da.copy(ta, t / CA);
             __builtin_amdgcn_sched_barrier(0);
         }
-        row_sums(0, 2 * s);
+        rs.add(a[0], 2 * s);
 #pragma unroll
         for (int t = 0; t < BP; ++t) {
             mma(1, t);
@@ -372,7 +399,7 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
             __builtin_amdgcn_sched_barrier(0);
         }
         if (MORE) db.next(g.b, tb);
-        row_sums(1, 2 * s + 1);
+        rs.add(a[1], 2 * s + 1);
         sA = sA1;
     };
     int s = 0;
@@ -388,18 +415,7 @@ __device__ __forceinline__ void wide_loop(const GemmArgs& g, unsigned char* smem
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j])::"memory");
-    if constexpr (RSUM) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) asm volatile("" : "+v"(rs[i])::"memory");
-        if (rsum) {
-            float* prow = g.c.rsum + (int64_t)(sidx * rs_nw + tn * 2 + wn) * g.c.rsum_ld;
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const int m = m0 + wm * 128 + i * 16 + lane;
-                if (lane < 16 && m < g.M) prow[m] = rs[i][0];
-            }
-        }
-    }
+    rs.store(g, m0 + wm * 128, sidx, tn, wn, lane);
 }
 
 // Float outputs (split partials, or fp32 C through a row map): 16-byte
@@ -510,7 +526,19 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&ac
     u32x4 bias_raw = {0u, 0u, 0u, 0u};
     if constexpr (ACT != 0)
         if (lane_on) bias_raw = *reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(e.act_bias) + n);
-    const bool biased = ACT == 0 && e.bias[0] != nullptr;
+    const bool biased = ACT == 0 && e.bias[0] != nullptr && !e.bias_on_m;
+    // a bias along m: the lane's row of each 16-row block
+    float bm[FM];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        bm[i] = 0.f;
+        if (ACT == 0 && e.bias[0] != nullptr && e.bias_on_m) {
+            const int m = mw + i * 16 + (lane & 15);
+            int sg = 0;
+            const int64_t bo = map_off(e.bias_map, (uint32_t)(m < g.M ? m : 0), e.bias_nseg, &sg);
+            bm[i] = to_f(reinterpret_cast<const T*>(pick(e.bias, sg))[bo]);
+        }
+    }
     unsigned char* wr = region + (lane & 15) * PITCH + (lane >> 4) * 8;
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
@@ -529,7 +557,7 @@ __device__ __forceinline__ void wide_store(const GemmArgs& g, const floatx4 (&ac
         for (int i = 0; i < FM; ++i) {
             T v[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = from_f<T>(ACT == 0 ? acc[i][j][r] + bn[r] : acc[i][j][r]);
+            for (int r = 0; r < 4; ++r) v[r] = from_f<T>(ACT == 0 ? acc[i][j][r] + (bn[r] + bm[i]) : acc[i][j][r]);
             *reinterpret_cast<u32x2*>(wr + i * 16 * PITCH + j * 32) = __builtin_bit_cast(u32x2, v);
         }
     }
@@ -626,8 +654,7 @@ template <typename T, int BN, bool AKC, bool BKC, bool RSUM, int EP>
 __device__ __forceinline__ void wide_block(const GemmArgs& g, unsigned char* smem, int tm, int tn, int sidx) {
     constexpr int FN = BN / 32;
     floatx4 acc[8][FN];
-    floatx4 rs[RSUM ? 8 : 1];
-    wide_loop<T, BN, AKC, BKC, RSUM>(g, smem, tm, tn, sidx, acc, rs);
+    wide_loop<T, BN, AKC, BKC, RSUM>(g, smem, tm, tn, sidx, acc);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int mw = tm * WBM + (w >> 1) * 128, nw = tn * BN + (w & 1) * (BN / 2);
     static_assert(4 * 128 * (FN * 32 + 16) <= 5 * SLOT && 16 * (FN * 64 + 16) <= SLOT, "staging regions");
@@ -657,7 +684,7 @@ __global__ __launch_bounds__(256) void gemm_wide(GemmArgs g) {
 // step s + 1; step s + 5 is copied into the freed slot, three of its eight
 // copies right after the barrier, the others during the next step's first
 // slice.  (4096 x 1024 x 4096 fp16: the lean 128x128 kernel 45 us.)
-template <typename T, bool AKC, bool BKC, int EP>
+template <typename T, bool AKC, bool BKC, int EP, bool RSUM>
 __device__ __forceinline__ void mid_block(const GemmArgs& g, unsigned char* smem, int tm, int tn, int sidx) {
     constexpr int BT = 128, FM = 4, FN = 4, NM = FM * FN, NR = FM + FN, BP = 4, ST = 5, HALF = SLOT / 2;
     typedef WideOp<T, BT, AKC, false> OA;
@@ -687,6 +714,7 @@ __device__ __forceinline__ void mid_block(const GemmArgs& g, unsigned char* smem
         else a[buf][j - FN] = __builtin_bit_cast(frag, OA::frag(st, wm * 64 + (j - FN) * 16, q, lane));
     };
     auto mma = [&](int buf, int t) { WMfma<T>::run(acc[t / FN][t % FN], b[buf][t % FN], a[buf][t / FN]); };
+    RowSums<T, FM, RSUM> rs(g, tn, wn);
     auto ta = da.first(g.a);
     auto tb = db.first(g.b);
     auto aim = [&](uint32_t slot, int c) {
@@ -738,6 +766,7 @@ __device__ __forceinline__ void mid_block(const GemmArgs& g, unsigned char* smem
             old_copy(t);
             __builtin_amdgcn_sched_barrier(0);
         }
+        rs.add(a[0], 2 * s);
 #pragma unroll
         for (int t = 0; t < BP; ++t) {
             mma(1, t);
@@ -766,6 +795,7 @@ __device__ __forceinline__ void mid_block(const GemmArgs& g, unsigned char* smem
             if (NEW && u % 4 == 1 && u / 4 < EARLY) copy(u / 4);
             __builtin_amdgcn_sched_barrier(0);
         }
+        rs.add(a[1], 2 * s + 1);
         last = at;
         at = nxt;
     };
@@ -784,13 +814,14 @@ __device__ __forceinline__ void mid_block(const GemmArgs& g, unsigned char* smem
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j])::"memory");
+    rs.store(g, m0 + wm * 64, sidx, tn, wn, lane);
     const int mw = m0 + wm * 64, nw = n0 + wn * 64;
     if constexpr (EP == 4) wide_store_f32<FM, FN>(g, acc, mw, nw, sidx);
     else if constexpr (EP == 3) wide_store_resid<T, FM, FN>(g, acc, mw, nw, smem + w * SLOT);
     else wide_store<T, FM, FN, EP>(g, acc, mw, nw, smem + w * SLOT);
 }
 
-template <typename T, bool AKC, bool BKC, int EP>
+template <typename T, bool AKC, bool BKC, int EP, bool RSUM = false>
 __global__ __launch_bounds__(256) void gemm_mid(GemmArgs g) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[5 * SLOT];
     const int nt = g.tiles_m * g.tiles_n, total = nt * (g.splits > 1 ? g.splits : 1);
@@ -799,7 +830,7 @@ __global__ __launch_bounds__(256) void gemm_mid(GemmArgs g) {
     const int sidx = lid / nt;
     int tm, tn;
     wide_tile(lid - sidx * nt, g.tiles_m, g.tiles_n, tm, tn);
-    mid_block<T, AKC, BKC, EP>(g, smem, tm, tn, sidx);
+    mid_block<T, AKC, BKC, EP, RSUM>(g, smem, tm, tn, sidx);
 }
 
 static_assert(offsetof(GemmGroup, g) == 0, "contraction p at p * sizeof(GemmArgs) of the kernel arguments");
@@ -885,6 +916,11 @@ template <typename T, bool AKC, bool BKC>
 void launch_mid_ep(const GemmArgs& g, hipStream_t st) {
     const dim3 grid(g.tiles_m * g.tiles_n * (g.splits > 1 ? g.splits : 1)), block(256);
     const int ep = g.splits > 1 || g.c.out_f32 ? 4 : g.c.act_mode ? g.c.act_mode : g.c.resid ? 3 : 0;
+    if constexpr (!AKC)
+        if (ep == 4 && g.c.rsum) {
+            hipLaunchKernelGGL((gemm_mid<T, false, BKC, 4, true>), grid, block, 0, st, g);
+            return;
+        }
     if (ep == 4) hipLaunchKernelGGL((gemm_mid<T, AKC, BKC, 4>), grid, block, 0, st, g);
     else if (ep == 3) hipLaunchKernelGGL((gemm_mid<T, AKC, BKC, 3>), grid, block, 0, st, g);
     else if (ep == 0) hipLaunchKernelGGL((gemm_mid<T, AKC, BKC, 0>), grid, block, 0, st, g);
@@ -926,12 +962,13 @@ bool operand_ok(const Operand& o, int64_t outer, int64_t K) {
 
 }  // namespace
 
-// Sizes are multiples of 8 (checked by the caller).  k in whole steps
+// Sizes are multiples of 8 (checked by the caller).  Row sums: the 128x128
+// tile (and the grouped launch) only.  k in whole steps
 // unless both operands are outer-contiguous (their k-rows past the end are
 // read as zeros).
 bool gemm_wide_ok(const GemmArgs& g, int bn) {
     const Epilogue& e = g.c;
-    if (g.batch != 1 || e.alpha != 1.0f || e.rsum || (g.a.kcontig && g.a.nseg > 1) || !operand_ok(g.a, g.M, g.K) ||
+    if (g.batch != 1 || e.alpha != 1.0f || (e.rsum && (bn != 128 || g.a.kcontig || !e.out_f32)) || (g.a.kcontig && g.a.nseg > 1) || !operand_ok(g.a, g.M, g.K) ||
         !operand_ok(g.b, g.N, g.K)) return false;
     if ((g.a.kcontig || g.b.kcontig) && g.K % WK) return false;
     if (bn == 192 && !g.b.kcontig) return false;
@@ -943,7 +980,7 @@ bool gemm_wide_ok(const GemmArgs& g, int bn) {
         if (!e.ptr[i] || (uintptr_t)e.ptr[i] % 16) return false;
     if (e.out_f32) return e.nmap.r0 == 0 && (e.nseg <= 1 || e.seg_on_m) && !e.resid && !e.bias[0];
     if (e.nmap.r0 % 8 || e.nmap.s1 % 8 || e.nmap.s2 % 8) return false;
-    if (e.bias[0] && (e.bias_on_m || e.resid || e.bias_map.r0 % 8)) return false;
+    if (e.bias[0] && (e.resid || (!e.bias_on_m && e.bias_map.r0 % 8))) return false;
     if (e.resid && (e.nseg != 1 || (uintptr_t)e.resid % 16)) return false;
     return true;
 }

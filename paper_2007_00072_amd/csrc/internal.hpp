@@ -155,7 +155,7 @@ struct AttnRows {
     int64_t outer, inner, ld;
 };
 bool attn_keys_ok(int dtype, int K, int P, int W, int path);
-size_t attn_keys_part_bytes(int B, int H, int J, int K);
+size_t attn_keys_part_bytes(int B, int H, int J, int K, int causal);
 void run_attn_bwd_keys(int dtype, int B, int H, int J, int K, float scaler, AttnRows q, AttnRows k, AttnRows v,
                        AttnRows dgamma, AttnRows gamma, const void* prob, const DropParams& dp, AttnRows dq,
                        AttnRows dk, AttnRows dv, float* part, hipStream_t st, int causal);

@@ -113,9 +113,9 @@ void plan_attention(const Dims& x, int mode, Carver& sv, Carver& fw, Carver& bw,
     p.dgamma = bw.take(es * x.Tq * x.H * x.W);
     // (dQ partials of the key-block backward: at most 4 B x 64 per query
     // row and 128-key block, no more than 2 B per score)
-    p.dalpha = bw.take(es * x.S > attn_keys_part_bytes((int)x.B, (int)x.H, (int)x.J, (int)x.K)
+    p.dalpha = bw.take(es * x.S > attn_keys_part_bytes((int)x.B, (int)x.H, (int)x.J, (int)x.K, x.causal)
                            ? es * x.S
-                           : attn_keys_part_bytes((int)x.B, (int)x.H, (int)x.J, (int)x.K));
+                           : attn_keys_part_bytes((int)x.B, (int)x.H, (int)x.J, (int)x.K, x.causal));
     p.dbeta = bw.take(es * x.S);
     p.alpha_b = bw.take(es * x.S);
     if (mode == PROJ_QKV) {
@@ -849,7 +849,10 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
         stacked_dx_args(x, DM_BJI, T, dqkv, 3, 0, 0, 3, prm, dx, dS1)};
     GemmGroup group;
     const int grouped = x.qkv_fusion == 0 && fl.dO_t != 1 && !fl.dH_t ? plan_gemm_group(dt, tail, 5, &group) : 0;
-    const bool have_dOT = !grouped && fl.dO_t != 0;
+    // (the library's own choice not for long ragged token sums: the wide
+    // kernels take a k that is no multiple of 64 only with both operands
+    // outer-contiguous; 1000 tokens: 12 us against 27 for the general kernel)
+    const bool have_dOT = !grouped && (fl.dO_t == 1 || (fl.dO_t == 2 && (T % 64 == 0 || T < 512)));
     l2.dsub_t = have_dOT ? dOT : nullptr;
     {
         TraceScope t_("B1-2 ln2_bwd", st);

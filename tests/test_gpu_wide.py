@@ -111,3 +111,16 @@ def test_group_and_separate_launches_agree(name, shape):
     for n, t in L1.grads.items():
         # T products per sum, fp32 accumulation in another order
         assert (g0[n] - t).abs().max().item() <= T ** 0.5 * 2.0 ** -20 * max(t.abs().max().item(), 1e-3), n
+
+
+@pytest.mark.parametrize("layout", ["ibj", "bji"])
+def test_mha_on_wide_tiles(layout):
+    # the paper's [i][b][j] order: outputs contiguous along the tokens run as
+    # their transposes (bias along m, stacked weights as the outer-contiguous
+    # first operand), the Q/K/V weight gradient with its row sums on 128x128
+    # tiles; 520 tokens: ragged last tiles
+    from paper_2007_00072_amd.inputs import WORKLOADS, Shape
+    from test_gpu_layer import check_mha
+    wl = WORKLOADS["mha_large_f16"].with_(shape=Shape(B=5, J=104, K=104, H=8, P=64, W=64, I=512), layout=layout, p_attn=0.1)
+    check_mha(wl, self_attention=True)
+    check_mha(wl, self_attention=2)
