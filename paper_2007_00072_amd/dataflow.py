@@ -57,6 +57,14 @@ REPLACES = {
 # Contractions the encoder layer issues as one launch (their tiles together
 # fill the chip): the backward's output-projection and Q/K/V weight gradients.
 PAIRED = {"B12+19 out_dw+qkv_dw": ("B12 out_dw", "B19 qkv_dw")}
+# Contractions the encoder backward issues as one launch after everything
+# else where their 256x256 tiles fill the chip: all four weight gradients,
+# with the Q/K/V input gradient where that pays (each runs in place of its
+# parts, PAIRED's among them).
+GROUPED = {
+    "B4+7+12+19 weight_grads": ("B4 linear2_dw", "B7 linear1_dw", "B12 out_dw", "B19 qkv_dw"),
+    "B4+7+12+18+19 weight_grads+qkv_dx": ("B4 linear2_dw", "B7 linear1_dw", "B12 out_dw", "B18 qkv_dx", "B19 qkv_dw"),
+}
 # Operators that run inside a contraction's epilogue where its kernel
 # allows (else as launches of their own): Linear 1 with bias + activation;
 # the input-bias gradient's partial sums inside the Q/K/V weight gradient
@@ -66,7 +74,7 @@ EPILOGUE = {"F7+8 linear1_bias_act": ("F7 linear1", "F8 bias_act"),
 FOLDED = {"B20 qkv_bias_grad": "B12+19 out_dw+qkv_dw"}
 # The launch sets one layer can run: every score step separate, scores on
 # chip, scores on chip with the next contraction in the same launch, and
-# that forward with the key-block backward (head size 64, K a multiple of 128).
+# that forward with the key-block backward (head size 64).
 PATHS = {
     "separate": (),
     "scores": ("F2-3 qkt_softmax", "B13-15 gamma_dx1_softmax_bwd"),
@@ -77,10 +85,11 @@ PATHS = {
 
 def key_blocks(s: Shape, dtype: str):
     """Key-block backward of the shape: (possible, key blocks per head)."""
-    if dtype == "f32" or s.P != 64 or s.W != 64 or s.K % 128:
+    if dtype == "f32" or s.P != 64 or s.W != 64 or s.K % 8:
         return False, 0
-    kg = 8 if s.K % 256 == 0 and s.B * s.H * (s.K // 256) >= 192 else 4
-    return True, s.K // (32 * kg)
+    n256, n128 = -(-s.K // 256), -(-s.K // 128)
+    eight = 2 * n256 == n128 and s.B * s.H * n256 >= 192
+    return True, n256 if eight else n128
 
 
 def path_groups(w: Dict[str, "Work"], path: str, epilogue=(), folded: bool = False) -> Dict[str, "Work"]:
@@ -88,7 +97,7 @@ def path_groups(w: Dict[str, "Work"], path: str, epilogue=(), folded: bool = Fal
     groups that ran, in place of their parts, True for all of them; folded:
     without the FOLDED launches)."""
     fused = PATHS[path]
-    gone = {p for f in fused for p in REPLACES[f]} | {p for parts in PAIRED.values() for p in parts}
+    gone = {p for f in fused for p in REPLACES[f]} | {p for parts in PAIRED.values() for p in parts} | set(GROUPED)
     ran = set(EPILOGUE) if epilogue is True else set(epilogue or ())
     for k, parts in EPILOGUE.items():
         gone |= set(parts) if k in ran else {k}
@@ -174,7 +183,7 @@ def encoder_layer(s: Shape, dtype: str, elements: bool = False) -> Dict[str, Wor
     w["B17 qkt_dx2"] = _att(Z, K, P, J, es, dtype, S, N)
     w["B18 qkv_dx"] = g(T, I, 3 * I, 3 * N, 3 * I * I, N, extra=N * es)      # + residual read
     w["B19 qkv_dw"] = g(3 * I, I, T, 3 * N, N, 3 * I * I, c_es=f4)
-    for lab, parts in PAIRED.items():
+    for lab, parts in {**PAIRED, **GROUPED}.items():
         w[lab] = Work(sum(w[p].flop for p in parts), sum(w[p].bytes for p in parts), "mfma", "contraction")
     w["B20 qkv_bias_grad"] = m(3 * N * es + 3 * I * f4)
     # column-sum partials of B1-2, B5, B8-10 and B20 finished in one launch

@@ -191,8 +191,9 @@ class _Layer:
         return {k: v / reps for k, v in tot.items()}
 
     def launches(self):
-        """(label, ContractChoice) of every contraction one step launches."""
-        from . import lib
+        """(label, ContractChoice) of every contraction one step launches by
+        itself (a plan's entry for one of a group's would end the group)."""
+        from . import dataflow, lib
         lib.dm_trace_enable(True)
         lib.plan_log(True)
         self.step()
@@ -200,7 +201,7 @@ class _Layer:
         recs = lib.plan_log_read()
         lib.plan_log(False)
         lib.dm_trace_enable(False)
-        return [(canonical(r.label.decode()), r) for r in recs]
+        return [(canonical(r.label.decode()), r) for r in recs if r.label.decode() not in dataflow.GROUPED]
 
 
 # Contractions that take an element-wise operator into their epilogue where
@@ -348,6 +349,10 @@ def tune(workload: str, reps: int = 3, log=print, shape=None, tile_cfgs=TILE_CFG
                 seen[eff] = sum(t for lab, t in tm.items() if names[lab] in sts)
         L.use((), 0, lay)
         builtin = next(((r.tile_cfg, r.splits) for lab, r in L.launches() if r.key() == key), None)
+        # (the library's own choice may be a kernel that no entry names)
+        if builtin is not None and builtin[0] not in TILE_CFGS:
+            tm = L.timed(reps)
+            seen[builtin] = sum(t for lab, t in tm.items() if stage_name(lab, lay) in sts)
         if builtin in seen:
             seen[builtin] *= KEEP_BUILTIN
         shape_costs[key] = seen
@@ -407,6 +412,8 @@ def tune(workload: str, reps: int = 3, log=print, shape=None, tile_cfgs=TILE_CFG
     result["lane_table"] = {str(k): round(v, 4) for k, v in lane_times.items()}
     entries = []
     for key, (cfg, sp) in chosen.items():
+        if cfg not in TILE_CFGS:
+            continue
         e = lib.ContractChoice(*key, cfg, sp)
         e.label = ",".join(where[key]).encode()[:47]
         entries.append(e)
@@ -435,17 +442,18 @@ def fusion_table(workload: str, reps: int = 3, shape=None):
     """Forward (Q/K/V projections) and backward (their dX and dW) time in
     ms of each projection grouping, built-in configurations (the analogue
     of the paper's algebraic-fusion table)."""
+    from . import dataflow
     out = {}
     for f in FUSIONS:
         L = _Layer(workload, shape, qkv_fusion=f)
         for _ in range(10):
             L.step()
         tm = L.timed(max(reps, 10))
-        # backward: dX and dW of the projections (the encoder launches the
-        # first group's dW together with the output projection's dW)
-        out[f] = {"forward": tm.get("F1 qkv", 0.0),
-                  "backward": tm.get("B18 qkv_dx", 0.0) + tm.get("B19 qkv_dw", 0.0) +
-                  tm.get("B12+19 out_dw+qkv_dw", 0.0)}
+        # backward: dX of the projections and every weight gradient (the
+        # encoder launches the projections' dW together with the others)
+        labels = {"B18 qkv_dx"} | {p for parts in dataflow.GROUPED.values() for p in parts}
+        labels |= set(dataflow.GROUPED) | set(dataflow.PAIRED)
+        out[f] = {"forward": tm.get("F1 qkv", 0.0), "backward": sum(tm.get(lab, 0.0) for lab in labels)}
         del L
     return out
 
