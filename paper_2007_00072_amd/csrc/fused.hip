@@ -20,13 +20,29 @@ namespace {
 
 constexpr int NT = 256;  // threads per block: 4 wave64s
 
+// 8 outputs of a contraction from its split partials, summed and rounded as
+// the contraction's own reduction does.
+template <typename T>
+__device__ __forceinline__ void split_sum8(const SplitSum& p, int64_t plane, int64_t at, float (&v)[8]) {
+    V8<float>::load(p.part + at, v);
+#pragma unroll 4
+    for (int s = 1; s < p.n; ++s) {
+        float t[8];
+        V8<float>::load(p.part + s * plane + at, t);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] += t[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = to_f(from_f<T>(v[q]));
+}
+
 // ------------------------------------------------------ bias+dropout+residual+LayerNorm
 template <typename T, int LPR, int NV>
 __global__ __launch_bounds__(NT) void bdrln_fwd_k(int64_t rows, int cols, const T* __restrict__ x,
                                                   const T* __restrict__ bias, const T* __restrict__ resid,
                                                   const T* __restrict__ gamma, const T* __restrict__ beta,
                                                   float eps, DropParams dp, T* __restrict__ y,
-                                                  T* __restrict__ xhat, float* __restrict__ rstd) {
+                                                  T* __restrict__ xhat, float* __restrict__ rstd, SplitSum xs) {
     constexpr int RPW = 64 / LPR;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gi = lane / LPR, gl = lane % LPR;
@@ -44,9 +60,10 @@ __global__ __launch_bounds__(NT) void bdrln_fwd_k(int64_t rows, int cols, const 
         const int c = (gl + i * LPR) * 8;
         if (active && c < cols) {
             float a[8], b[8], r[8];
-            V8<T>::load(x + base + c, a);
             V8<T>::load(bias + c, b);
             V8<T>::load(resid + base + c, r);
+            if (xs.n) split_sum8<T>(xs, (int64_t)rows * cols, base + c, a);
+            else V8<T>::load(x + base + c, a);
 #pragma unroll
             for (int q = 0; q < 8; ++q) a[q] += b[q];
             dropout8(dp, (uint64_t)(base + c), a);
@@ -681,13 +698,13 @@ int grid_for(int64_t nvec) {
 template <typename T>
 void bdrln_t(int64_t rows, int len, const void* x, const void* bias, const void* resid, const void* gamma,
              const void* beta, float eps, const DropParams& dp, void* y, void* xhat, float* rstd,
-             int lanes, hipStream_t st) {
+             int lanes, SplitSum xs, hipStream_t st) {
 #define L(LPR, NV)                                                                              \
     {                                                                                           \
         int64_t rpb = 4 * (64 / LPR);                                                           \
         hipLaunchKernelGGL((bdrln_fwd_k<T, LPR, NV>), dim3((rows + rpb - 1) / rpb), dim3(NT), 0, \
                            st, rows, len, (const T*)x, (const T*)bias, (const T*)resid,         \
-                           (const T*)gamma, (const T*)beta, eps, dp, (T*)y, (T*)xhat, rstd);    \
+                           (const T*)gamma, (const T*)beta, eps, dp, (T*)y, (T*)xhat, rstd, xs); \
     }
     DM_ROW_CASES_LANES(lanes, L)
 #undef L
@@ -785,7 +802,7 @@ __global__ __launch_bounds__(NTL) void ln_bwd_cs_k(LnBwdArgs a, int nblk) {
         for (int p = 0; p < NP; ++p) {
             const int64_t row = t0 + p * RPP + gi;
             const int64_t rr = row < a.rows ? row : t0;
-            ldy[p] = *reinterpret_cast<const u32x4*>(dya + rr * cols + c);
+            if (!a.dya_s.n) ldy[p] = *reinterpret_cast<const u32x4*>(dya + rr * cols + c);
             lxh[p] = *reinterpret_cast<const u32x4*>(xhat + rr * cols + c);
             if (dyb) ldb[p] = *reinterpret_cast<const u32x4*>(dyb + rr * cols + c);
             rs[p] = do_ds ? a.rstd[rr] : 0.f;
@@ -793,7 +810,12 @@ __global__ __launch_bounds__(NTL) void ln_bwd_cs_k(LnBwdArgs a, int nblk) {
         float dy[NP][8], xh[NP][8];
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            V8<T>::unpack(ldy[p], dy[p]);
+            if (a.dya_s.n) {
+                const int64_t row = t0 + p * RPP + gi;
+                split_sum8<T>(a.dya_s, a.rows * cols, (row < a.rows ? row : t0) * cols + c, dy[p]);
+            } else {
+                V8<T>::unpack(ldy[p], dy[p]);
+            }
             V8<T>::unpack(lxh[p], xh[p]);
             if (dyb) {
                 float t[8];
@@ -950,8 +972,8 @@ int ln_bwd_blocks(int64_t rows, int cols, int dtype, int form) {
 
 void run_bdrln_fwd(int dtype, int64_t rows, int cols, const void* x, const void* bias, const void* resid,
                    const void* gamma, const void* beta, float eps, const DropParams& dp, void* y, void* xhat,
-                   float* rstd, hipStream_t st, int lanes) {
-    DM_DTYPE_SWITCH(dtype, bdrln_t<T>(rows, cols, x, bias, resid, gamma, beta, eps, dp, y, xhat, rstd, lanes, st));
+                   float* rstd, hipStream_t st, int lanes, SplitSum xs) {
+    DM_DTYPE_SWITCH(dtype, bdrln_t<T>(rows, cols, x, bias, resid, gamma, beta, eps, dp, y, xhat, rstd, lanes, xs, st));
 }
 
 void run_softmax_fwd(int dtype, int B, int H, int J, int K, float scale, const void* beta, const DropParams& dp,

@@ -106,6 +106,7 @@ struct GemmArgs {
     float* split_ws;       // splits * batch * M * N floats of partial sums
     int64_t split_cap;     // floats available at split_ws
     int kper;              // k range per split (set by the launcher)
+    int defer;             // the caller's next kernel may sum the split partials (gemm_deferred_splits)
     int cfg;               // tile configuration index; < 0 lets the launcher choose
     // set by the launcher: outputs at coff(z) + m * ldc + n (contig_n) or
     // coff(z) + m + n * ldc, one pointer; bias_mode 0 none, 1 along the
@@ -124,6 +125,12 @@ struct GemmArgs {
 // Number of Epilogue::rsum partial rows the last launch_gemm on this
 // thread wrote (for launch_gemm_pair: its first contraction's), 0 if none.
 int gemm_rowsum_parts();
+
+// Split partials the last launch_gemm on this thread left unsummed at
+// split_ws (splits planes of M x N floats; the output is not written), 0 if
+// it wrote its output.  Only for a GemmArgs::defer request with a plain
+// row-major 16-bit output (no bias, residual or activation step, alpha 1).
+int gemm_deferred_splits();
 
 // Whether launch_gemm would run this contraction with the staged epilogue
 // that takes its Epilogue::act_mode step (otherwise the request is ignored

@@ -2252,7 +2252,7 @@ void launch_t(const GemmArgs& g, hipStream_t st) {
         case 3: launch_cfg<T, 256, 64, 4, 1, 1>(g, st); break;
         default: launch_cfg<T, 128, 64, 2, 2, 1>(g, st); break;
     }
-    if (g.splits > 1) launch_reduce<T>(g, st);
+    if (g.splits > 1 && !g.defer) launch_reduce<T>(g, st);
 }
 
 }  // namespace

@@ -94,13 +94,22 @@ struct FusedLayout {
 };
 FusedLayout fused_layout(int dtype, int64_t T, int I, int F);
 
+// A contraction's output as n planes of fp32 split partials (n = 0: it is in
+// its own buffer).
+struct SplitSum {
+    const float* part;
+    int n;
+};
+
 // ------------------------------------------------------- kernel launchers
 // All take element counts, device pointers and a stream, and assume the
 // caller validated alignment and sizes.  dtype: DM_F32 / DM_F16 / DM_BF16.
 // lanes: lanes per row (0 = by row length; 16, 32 for rows of 257..1024)
+// xs: x as the split partials a contraction left (16-bit types; x unused)
 void run_bdrln_fwd(int dtype, int64_t rows, int cols, const void* x, const void* bias,
                    const void* resid, const void* gamma, const void* beta, float eps,
-                   const DropParams& dp, void* y, void* xhat, float* rstd, hipStream_t st, int lanes = 0);
+                   const DropParams& dp, void* y, void* xhat, float* rstd, hipStream_t st, int lanes = 0,
+                   SplitSum xs = SplitSum{});
 
 // Attention scores without the score tensor in HBM (attn.hip).  Operand
 // element (z = b*H + h, row r, contraction index d) sits at
@@ -196,6 +205,7 @@ struct LnBwdArgs {
     void* dsub_t;  // optional [cols][rows] copy of dsub (written when the column-split form runs)
     int form;      // 0 library's choice, 1 row form, 2 column split (ln_bwd_uses_split)
     int lanes;     // row form: lanes per row (0 = by row length)
+    SplitSum dya_s;  // column-split form: dya as split partials (dya unused)
 };
 void run_ln_bwd(const LnBwdArgs& a, hipStream_t st);
 

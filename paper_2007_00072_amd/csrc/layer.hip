@@ -299,6 +299,16 @@ GemmArgs gemm(int64_t M, int64_t N, int64_t K, int64_t batch, const Operand& a, 
     return g;
 }
 
+// A contraction whose consumer can sum its split partials itself (parts not
+// null; parts->n = 0 if the output was written all the same): the
+// reduction's launch and its pass over the output are left out.
+int split_gemm(int dtype, GemmArgs g, SplitSum* parts, hipStream_t st) {
+    g.defer = parts != nullptr;
+    DM_TRY(launch_gemm(dtype, g, st));
+    if (parts) *parts = SplitSum{g.split_ws, gemm_deferred_splits()};
+    return DM_OK;
+}
+
 // An activation x (t, i) in the given layout, as the (m, k) operand with m = t, k = i...
 Operand act_mk(const void* p, int layout, int64_t T, int64_t I) {
     return layout == DM_BJI ? opnd(p, true, linear_map(I)) : opnd(p, false, linear_map(T));
@@ -434,15 +444,16 @@ int attention_core_fwd(const Dims& x, float scaler, const DropParams& dp, const 
 }
 
 // out(t, i) = sum_{h,w} gamma[t][(h,w)] wo[w][h][i] (+ bo)
+// (parts: the caller's next kernel sums split partials, see split_of)
 int out_projection(const Dims& x, const void* gamma, const void* wo, const void* bo, void* out, int layout,
-                   hipStream_t st) {
+                   hipStream_t st, SplitSum* parts = nullptr) {
     const int64_t HW = x.H * x.W;
     Operand A = opnd(gamma, true, linear_map(HW));
     Operand Bw = opnd(wo, false, make_map((uint32_t)x.W, 0, x.H * x.I, x.I, 0));
     Epilogue c = act_out(out, layout, x.Tq, x.I);
     if (bo) { c.bias[0] = bo; c.bias_map = linear_map(1); }
     TraceScope t_("F5 out", st);
-    return launch_gemm(x.dtype, gemm(x.Tq, x.I, HW, 1, A, Bw, c), st);
+    return split_gemm(x.dtype, gemm(x.Tq, x.I, HW, 1, A, Bw, c), parts, st);
 }
 
 // Backward of attention from d(out) (layout `layout`) down to the gradients
@@ -738,13 +749,15 @@ int encoder_layer_fwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
     DM_TRY(attention_core_fwd(x, scaler_of(d), make_drop(d->p_attn, d->seed, 0, d->layer_id), q, k, v, beta, prob,
                               alpha, gamma, gamma32, st));
     // Out
-    DM_TRY(out_projection(x, gamma, prm->wo, nullptr, ao, DM_BJI, st));
+    SplitSum parts{};
+    DM_TRY(out_projection(x, gamma, prm->wo, nullptr, ao, DM_BJI, st, &parts));
     const FusedLayout fl = fused_layout(dt, T, (int)x.I, (int)x.F);
     // bias + dropout + residual + LayerNorm 1
     {
         TraceScope t_("F6 bdrln1", st);
         run_bdrln_fwd(dt, T, (int)x.I, ao, prm->bo, x_in, prm->g1, prm->be1, d->ln_eps,
-                      make_drop(d->p_attn_out, d->seed, 1, d->layer_id), y1, xhat1, rstd1, st, fl.ln_lanes);
+                      make_drop(d->p_attn_out, d->seed, 1, d->layer_id), y1, xhat1, rstd1, st, fl.ln_lanes,
+                      parts);
     }
     DM_TRY(check_launch("bdrln 1"));
     // Linear 1, with bias + activation (+ dropout) in its epilogue where
@@ -772,16 +785,16 @@ int encoder_layer_fwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
     // Linear 2
     {
         TraceScope t_("F9 linear2", st);
-        DM_TRY(launch_gemm(dt,
-                           gemm(T, x.I, x.F, 1, opnd(abuf, true, linear_map(x.F)),
-                                opnd(prm->w2, true, linear_map(x.F)),
-                                epi(o, linear_map(x.I), linear_map(1), true, false)),
-                           st));
+        DM_TRY(split_gemm(dt,
+                          gemm(T, x.I, x.F, 1, opnd(abuf, true, linear_map(x.F)),
+                               opnd(prm->w2, true, linear_map(x.F)),
+                               epi(o, linear_map(x.I), linear_map(1), true, false)),
+                          &parts, st));
     }
     // bias + dropout + residual + LayerNorm 2
     TraceScope t10("F10 bdrln2", st);
     run_bdrln_fwd(dt, T, (int)x.I, o, prm->b2, y1, prm->g2, prm->be2, d->ln_eps,
-                  make_drop(d->p_ffn_out, d->seed, 2, d->layer_id), y, xhat2, rstd2, st, fl.ln_lanes);
+                  make_drop(d->p_ffn_out, d->seed, 2, d->layer_id), y, xhat2, rstd2, st, fl.ln_lanes, parts);
     return check_launch("bdrln 2");
 }
 
@@ -898,14 +911,7 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
         run_act_bwd(dt, T, (int)F, dA, hbuf, prm->b1, d->act, g3.c.act_dp, dH, part_act, st, dHT);
     }
     DM_TRY(check_launch("activation backward"));
-    // Linear 1 dX and dW
-    {
-        TraceScope t_("B6 linear1_dx", st);
-        DM_TRY(launch_gemm(dt,
-                           gemm(T, I, F, 1, opnd(dH, true, linear_map(F)), opnd(prm->w1, false, linear_map(I)),
-                                epi(dY1f, linear_map(I), linear_map(1), true, false)),
-                           st));
-    }
+    // Linear 1 dW and dX
     if (!grouped) {
         TraceScope t_("B7 linear1_dw", st);
         const Operand a_op = dHT ? opnd(dHT, true, linear_map(T)) : opnd(dH, false, linear_map(F));
@@ -914,11 +920,21 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
                                 epi(g->dw1, linear_map(I), linear_map(1), true, true)),
                            st));
     }
+    // (last before its reader: the LayerNorm backward sums its split partials)
+    SplitSum dY1f_parts{};
+    {
+        TraceScope t_("B6 linear1_dx", st);
+        DM_TRY(split_gemm(dt,
+                          gemm(T, I, F, 1, opnd(dH, true, linear_map(F)), opnd(prm->w1, false, linear_map(I)),
+                               epi(dY1f, linear_map(I), linear_map(1), true, false)),
+                          ln_bwd_uses_split((int)I, dt, fl.ln_form) ? &dY1f_parts : nullptr, st));
+    }
     // residual + LayerNorm-1 scale/shift grads, LayerNorm-1 dX, dropout dX, output-bias grad
     LnBwdArgs l1{};
     l1.dtype = dt; l1.rows = T; l1.cols = (int)I; l1.dya = dY1f; l1.dyb = dS2; l1.xhat = xhat1; l1.gamma = prm->g1;
     l1.rstd = rstd1; l1.dp = make_drop(d->p_attn_out, d->seed, 1, d->layer_id); l1.ds = dS1; l1.dsub = dAO;
     l1.part = part_ln1; l1.want_dsub_sum = 1; l1.form = fl.ln_form; l1.lanes = fl.ln_lanes;
+    l1.dya_s = dY1f_parts;
     {
         TraceScope t_("B8-10 ln1_bwd", st);
         run_ln_bwd(l1, st);
