@@ -338,7 +338,7 @@ int contract(int32_t dtype, int32_t batch, int32_t M, int32_t N, int32_t K, floa
  * descriptor names it.  A contraction is identified by its sizes, dtype and
  * which operands are contiguous along the contraction index
  * (dm_contract_choice without the label); a plan entry sets its tile_cfg
- * (0..19, as for contract) and split factor (1 = none; larger values are cut
+ * (0..25, as for contract) and split factor (1 = none; larger values are cut
  * to what the call's split-k scratch holds).  Entries that a contraction's
  * operands or epilogue do not allow fall back the way contract's tile_cfg
  * does, so a plan never changes results beyond the order of the fp32
@@ -355,14 +355,15 @@ int contract(int32_t dtype, int32_t batch, int32_t M, int32_t N, int32_t K, floa
  *
  * plan_log(1) clears and starts a record of the contractions the calling
  * thread's layer and attention calls launch (sizes, dtype, operand
- * contiguity, the tile_cfg and splits that ran, and the kernel-timing label
- * when timing is on); plan_log(0) stops it; plan_log_read copies up to `cap`
+ * contiguity, the tile_cfg and splits that ran (26..28: kernels that only the
+ * library's own choice runs, 256x256, 256x192 and 128x128 tiles; -1: float32),
+ * and the kernel-timing label when timing is on); plan_log(0) stops it; plan_log_read copies up to `cap`
  * records of the calling thread and sets *count to the number recorded. */
 typedef struct {
     int64_t M, N, K, batch;        /* contraction sizes; batch: contractions in one launch */
     int32_t dtype;                 /* dm_dtype                                             */
     int32_t a_kcontig, b_kcontig;  /* 1: operand contiguous along the contraction index   */
-    int32_t tile_cfg;              /* 0..25 (contract's list)                              */
+    int32_t tile_cfg;              /* 0..25 (contract's list); a log record also -1, 26..28 */
     int32_t splits;                /* split-k factor, 1 = none                             */
     char label[48];                /* log only: kernel-timing label, "" when timing is off */
 } dm_contract_choice;

@@ -1,7 +1,7 @@
 // Contractions, host side: validation, plan and configuration choice of
 // every launch, and the float32 kernel.  The 16-bit kernels are in
 // gemm_kernels.hpp, compiled for each storage type by gemm_f16.hip and
-// gemm_bf16.hip.
+// gemm_bf16.hip, and in gemm_wide.hip.
 #include <algorithm>
 #include <mutex>
 #include <string.h>
@@ -205,11 +205,11 @@ int64_t ntiles(const TileCfg& c, const GemmArgs& g) {
 }
 
 // Tile and split choice, from measurements of the layer's contraction
-// shapes on MI355X (every configuration x split 1/2/4): the lean 256x256
-// kernel (ping-pong schedule) when that tile alone gives (nearly) every CU
-// a block; otherwise the
-// lean 128x128 kernel, split along k for long-k contractions with few
-// output tiles (up to four ways, towards one block per CU); narrow outputs
+// shapes on MI355X (every configuration x split 1/2/4): 256x256 tiles when
+// they alone give (nearly) every CU a block, otherwise 128x128 tiles, split
+// along k for long-k contractions with few output tiles (up to four ways,
+// towards one block per CU), each on the wide kernel where that takes the
+// contraction and on the lean one otherwise; narrow outputs
 // (n <= 64) on the asynchronous 128x64 tile.  A lean kernel hands
 // contractions it does not take to its general counterpart.  Explicit
 // choices (cfg >= 0, splits > 0) are kept.

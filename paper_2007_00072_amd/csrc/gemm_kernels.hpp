@@ -1,5 +1,6 @@
-// MFMA contraction kernel for gfx950 (fp16 / bf16 storage, fp32
-// accumulation) and an fp32 MFMA kernel (v_mfma_f32_32x32x2f32) for float32 layers.
+// MFMA contraction kernels for gfx950 (fp16 / bf16 storage, fp32
+// accumulation): every layout and size; the sizes that fill the chip run on
+// gemm_wide.hip's kernels where those take the operands.
 //
 // Block tile BM x BN (256x256 down to 128x64), k-step 64, 4 or 8 wave64s in
 // a WGM x WGN grid of wave tiles, v_mfma_f32_16x16x32 inner products.
@@ -18,8 +19,9 @@
 //
 // Tiles are numbered so that each of the 8 XCDs gets a contiguous run of
 // tile indices, walked in groups of rows for L2 reuse.  A split-K mode
-// writes float partial sums that a second kernel adds in a fixed order
-// (deterministic), for contractions with few output tiles and a long k.
+// writes float partial sums that a second kernel (or the LayerNorm kernel
+// that reads the result) adds in a fixed order (deterministic), for
+// contractions with few output tiles and a long k.
 #pragma once
 
 #include "gemm.hpp"

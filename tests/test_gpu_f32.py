@@ -16,7 +16,7 @@ def test_f32_contract_edges(a_trans, b_trans, batch, M, N, K):
     A = make_tensor((batch, K, M) if a_trans else (batch, M, K), "f32", 21).cuda()
     B = make_tensor((batch, N, K) if b_trans else (batch, K, N), "f32", 22).cuda()
     bias = make_tensor((N,), "f32", 23).cuda()
-    C = torch.full((batch * M * N + 8,), 7.0, device="cuda")
+    C = torch.full((batch * M * N + 8,), 7.0, dtype=torch.float32, device="cuda")
     lib.contract(lib.DM_F32, batch, M, N, K, 0.5, A, a_trans, M * K, B, b_trans, N * K, bias, C, 0, M * N)
     torch.cuda.synchronize()
     a = (A.transpose(1, 2) if a_trans else A).double().contiguous()
