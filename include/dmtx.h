@@ -338,11 +338,19 @@ int contract(int32_t dtype, int32_t batch, int32_t M, int32_t N, int32_t K, floa
  * descriptor names it.  A contraction is identified by its sizes, dtype and
  * which operands are contiguous along the contraction index
  * (dm_contract_choice without the label); a plan entry sets its tile_cfg
- * (0..25, as for contract) and split factor (1 = none; larger values are cut
- * to what the call's split-k scratch holds).  Entries that a contraction's
+ * (0..25, as for contract; 26, 27, 28, where K >= 512 or M or N > 128: the
+ * kernels that the library itself mostly runs from there up, one wave per
+ * SIMD and 64-wide k-steps in five LDS slots on 256x256, 256x192 (B contiguous
+ * along k) and 128x128 tiles; as 23, 25 and 15 where they do not take the
+ * contraction) and split factor (1 = none; larger values are cut to what the
+ * call's split-k scratch holds).  Entries that a contraction's
  * operands or epilogue do not allow fall back the way contract's tile_cfg
  * does, so a plan never changes results beyond the order of the fp32
- * accumulation.  attn_path: 0 = automatic, 1 = QK^T, softmax + dropout and
+ * accumulation.  The encoder backward's weight gradients share one launch
+ * of 256x256 tiles, with the Q/K/V input gradient or without, where that is
+ * expected to be faster, unless an entry names one of them with another
+ * tile_cfg than 26 or with a split factor of its own (the input gradient
+ * alone leaves the others together).  attn_path: 0 = automatic, 1 = QK^T, softmax + dropout and
  * Gamma (and their backward steps) as separate launches, 2 = scores kept on
  * chip (QK^T with softmax + dropout, Gamma dX1 with its backward), 3 = as 2
  * with Gamma and QK^T dX1 in the same launches; a grouping a shape does not
@@ -355,15 +363,15 @@ int contract(int32_t dtype, int32_t batch, int32_t M, int32_t N, int32_t K, floa
  *
  * plan_log(1) clears and starts a record of the contractions the calling
  * thread's layer and attention calls launch (sizes, dtype, operand
- * contiguity, the tile_cfg and splits that ran (26..28: kernels that only the
- * library's own choice runs, 256x256, 256x192 and 128x128 tiles; -1: float32),
- * and the kernel-timing label when timing is on); plan_log(0) stops it; plan_log_read copies up to `cap`
- * records of the calling thread and sets *count to the number recorded. */
+ * contiguity, the tile_cfg and splits that ran (-1: float32), and the
+ * kernel-timing label when timing is on); plan_log(0) stops it; plan_log_read
+ * copies up to `cap` records of the calling thread and sets *count to the
+ * number recorded.  Records of 16-bit contractions are valid plan entries. */
 typedef struct {
     int64_t M, N, K, batch;        /* contraction sizes; batch: contractions in one launch */
     int32_t dtype;                 /* dm_dtype                                             */
     int32_t a_kcontig, b_kcontig;  /* 1: operand contiguous along the contraction index   */
-    int32_t tile_cfg;              /* 0..25 (contract's list); a log record also -1, 26..28 */
+    int32_t tile_cfg;              /* 0..25 (contract's list), 26..28; a log record also -1 */
     int32_t splits;                /* split-k factor, 1 = none                             */
     char label[48];                /* log only: kernel-timing label, "" when timing is off */
 } dm_contract_choice;

@@ -159,7 +159,8 @@ int plan_create(const dm_contract_choice* entries, int32_t n, int32_t attn_path,
     if (attn_path < 0 || attn_path > 3) return set_error(DM_ERR_ARG, "attn_path %d outside [0, 3]", attn_path);
     for (int i = 0; i < n; ++i) {
         const dm_contract_choice& e = entries[i];
-        if (e.tile_cfg < 0 || e.tile_cfg > GEMM_MAX_CFG)
+        if (e.tile_cfg < 0 || e.tile_cfg > GEMM_CFG_MID ||
+            (e.tile_cfg > GEMM_MAX_CFG && !gemm_plan_wide_ok(e.M, e.N, e.K)))
             return set_error(DM_ERR_ARG, "plan entry %d: tile_cfg %d", i, e.tile_cfg);
         if (e.splits < 1 || e.splits > 64) return set_error(DM_ERR_ARG, "plan entry %d: splits %d", i, e.splits);
         if (e.M <= 0 || e.N <= 0 || e.K <= 0 || e.batch <= 0) return set_error(DM_ERR_ARG, "plan entry %d: sizes", i);

@@ -190,7 +190,8 @@ struct TileCfg {
 // (4 wave rows, 2 columns), for a B operand contiguous along k (otherwise
 // run as 23): 3072-wide outputs get 16 x 16 tiles, every CU one.  26, 27,
 // 28: the wide kernels (gemm_wide.hip), 256x256, 256x192 and 128x128; the
-// library's own choices only.
+// library's own choices and plan entries' only; contractions they do not take
+// run as 23, 25 and 15 would.
 constexpr TileCfg CFGS[] = {{256, 256, 2, 4}, {256, 128, 2, 2}, {128, 128, 2, 2}, {256, 64, 4, 1}, {128, 64, 2, 2},
                             {256, 128, 2, 2}, {128, 128, 2, 2}, {256, 64, 4, 1}, {128, 64, 2, 2},
                             {256, 256, 2, 4}, {256, 128, 2, 2}, {128, 128, 2, 2}, {256, 128, 4, 2},
@@ -257,11 +258,6 @@ void choose(GemmArgs& g) {
             if (g.splits <= 1 && g.K >= 512 && gemm_wide_ok(g, 128)) g.cfg = GEMM_CFG_MID;
         }
     }
-    // the 32x32x16 kernels' epilogues take no bias along m and only output
-    // maps affine over 32-wide blocks; of them only the lean 128x128 kernel
-    // takes a residual operand
-    if (((g.c.bias[0] && g.c.bias_on_m) || !g.blk32) && g.cfg >= 9 && g.cfg < GEMM_CFG_WIDE) g.cfg = 8;
-    if (g.c.resid && g.cfg >= 9 && g.cfg < GEMM_CFG_WIDE && g.cfg != 15 && g.cfg != 16 && g.cfg != 18 && g.cfg != 22) g.cfg = 8;
     if (g.splits <= 0) {
         int s = split_ok ? want_split : 1;
         while (s > 1 && (g.K / s < min_k || (int64_t)s * g.batch * g.M * g.N > g.split_cap)) --s;
@@ -272,6 +268,14 @@ void choose(GemmArgs& g) {
         g.kper = (ksteps + g.splits - 1) / g.splits * BK;
         g.splits = (g.K + g.kper - 1) / g.kper;
     }
+    // a wide kernel that a plan names for what it does not take
+    if (g.cfg >= GEMM_CFG_WIDE && !gemm_wide_ok(g, CFGS[g.cfg].bn))
+        g.cfg = g.cfg == GEMM_CFG_WIDE ? 23 : g.cfg == GEMM_CFG_WIDE192 ? 25 : 15;
+    // the 32x32x16 kernels' epilogues take no bias along m and only output
+    // maps affine over 32-wide blocks; of them only the lean 128x128 kernel
+    // takes a residual operand
+    if (((g.c.bias[0] && g.c.bias_on_m) || !g.blk32) && g.cfg >= 9 && g.cfg < GEMM_CFG_WIDE) g.cfg = 8;
+    if (g.c.resid && g.cfg >= 9 && g.cfg < GEMM_CFG_WIDE && g.cfg != 15 && g.cfg != 16 && g.cfg != 18 && g.cfg != 22) g.cfg = 8;
     if (g.cfg == 19 && !g.b.kcontig) g.cfg = 13;
     if (g.cfg == 21 && !g.b.kcontig) g.cfg = 20;
     if (g.cfg == 25 && !g.b.kcontig) g.cfg = 23;
@@ -342,19 +346,26 @@ bool same_contraction(const dm_contract_choice& e, const GemmArgs& g, int dtype)
            e.a_kcontig == (g.a.kcontig ? 1 : 0) && e.b_kcontig == (g.b.kcontig ? 1 : 0);
 }
 
+// The running plan's entry for this contraction (the first), if any.
+const dm_contract_choice* plan_entry(const GemmArgs& g, int dtype) {
+    if (!t_plan) return nullptr;
+    for (const dm_contract_choice& e : t_plan->entries)
+        if (same_contraction(e, g, dtype)) return &e;
+    return nullptr;
+}
+
 // A plan entry's tile and split factor for an automatically configured
-// contraction; the split factor is cut to what the scratch holds.
+// contraction; the split factor is cut to what the scratch holds and to
+// pieces of 256 of k (128 where the next kernel sums the partials: what
+// choose() itself goes down to there).
 void apply_plan(GemmArgs& g, int dtype) {
-    if (!t_plan) return;
-    for (const dm_contract_choice& e : t_plan->entries) {
-        if (!same_contraction(e, g, dtype)) continue;
-        g.cfg = e.tile_cfg;
-        int s = e.splits > 1 ? e.splits : 1;
-        if (!g.split_ws || g.batch != 1) s = 1;
-        while (s > 1 && (g.K / s < 256 || (int64_t)s * g.batch * g.M * g.N > g.split_cap)) --s;
-        g.splits = s;
-        return;
-    }
+    const dm_contract_choice* e = plan_entry(g, dtype);
+    if (!e) return;
+    g.cfg = e->tile_cfg;
+    int s = e->splits > 1 ? e->splits : 1;
+    if (!g.split_ws || g.batch != 1) s = 1;
+    while (s > 1 && (g.K / s < (g.defer ? 128 : 256) || (int64_t)s * g.batch * g.M * g.N > g.split_cap)) --s;
+    g.splits = s;
 }
 
 // Keeps the activation step only where the staged epilogue takes it:
@@ -488,7 +499,7 @@ static int prepare(GemmArgs& g, int dtype, bool pair) {
     if (g.cfg < 0) apply_plan(g, dtype);
     // an output contiguous along m (the paper's [i][b][j] order) as its
     // transpose, where the wide kernels then take it: they store along n
-    if (g.cfg < 0 && !pair && !g.c.contig_n && !g.c.rsum && !g.c.act_mode && g.batch == 1 && g.K >= 512 && g.M > 64) {
+    if ((g.cfg < 0 || g.cfg >= GEMM_CFG_WIDE) && !pair && !g.c.contig_n && !g.c.rsum && !g.c.act_mode && g.batch == 1 && g.K >= 512 && g.M > 64) {
         GemmArgs t = transposed(g);
         set_affine(t);
         set_ep_stage(t);
@@ -588,13 +599,19 @@ int plan_gemm_group(int dtype, const GemmArgs* gs, int n, GemmGroup* grp) {
     double separate = 0, expect_input = 0;
     int64_t nw = 0, nb = 0;
     int kw = 0, kb = 0, weights = 0;
+    int want = 0;  // split factor that the plan names for the weight gradients
     for (int i = 0; i < n; ++i) {
         GemmArgs& g = grp->g[i];
         g = gs[i];
         if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.M % 8 || g.N % 8 || g.K % 8) return 0;
-        if (t_plan)
-            for (const dm_contract_choice& e : t_plan->entries)
-                if (same_contraction(e, g, dtype)) return 0;
+        // (entries may name what a grouped launch reports; one that gives the
+        // input gradient another kernel leaves only that one out)
+        bool own_launch = false;
+        if (const dm_contract_choice* e = plan_entry(g, dtype)) {
+            own_launch = e->tile_cfg != GEMM_CFG_WIDE || (g.a.kcontig ? e->splits > 1 : want && want != e->splits);
+            if (own_launch && !g.a.kcontig) return 0;
+            if (!g.a.kcontig) want = e->splits;
+        }
         set_affine(g);
         set_ep_stage(g);
         g.splits = 1;
@@ -613,7 +630,7 @@ int plan_gemm_group(int dtype, const GemmArgs* gs, int n, GemmGroup* grp) {
             ++weights;
         } else {
             if (i != n - 1 || g.b.kcontig || g.c.out_f32 || !g.c.resid) return 0;
-            nb = (int64_t)g.tiles_m * g.tiles_n;
+            nb = own_launch ? 0 : (int64_t)g.tiles_m * g.tiles_n;
             kb = g.K;
             expect_input = single;
         }
@@ -632,6 +649,7 @@ int plan_gemm_group(int dtype, const GemmArgs* gs, int n, GemmGroup* grp) {
         for (int i = 0; i < weights; ++i) outs += (int64_t)gs[i].M * gs[i].N;
         floats = s * outs;
         if (s > 1 && floats > gs[0].split_cap) break;
+        if (want && s != want) continue;
         const double tw = WIDE_STEP * (kper / 64) + WIDE_FIX;
         const double red = s > 1 ? LAUNCH + 2.0 * floats * 4 / 4e6 : 0;
         // (a grid that leaves more than a quarter of the CUs idle is left to

@@ -140,10 +140,17 @@ bool gemm_act_fusable(int dtype, const GemmArgs& g);
 // act_mode 2 (0 if none).
 int gemm_act_parts();
 
-// Largest tile configuration index a caller may name (contract's tile_cfg,
-// plan entries), and the library's own choices beyond it.
+// Largest tile configuration index contract's tile_cfg may name, and the wide
+// kernels (gemm_wide.hip) beyond it: the library's own choices, and plan
+// entries', so that what plan_log reports can be given back as a plan.
 constexpr int GEMM_MAX_CFG = 25;
 constexpr int GEMM_CFG_WIDE = 26, GEMM_CFG_WIDE192 = 27, GEMM_CFG_MID = 28;
+
+// Whether a plan entry may name the wide kernels for these sizes: wherever
+// the library itself may run them (alone from k = 512 or 192 tiles of
+// 256x256 up, grouped from a width above 256 or k = 1024 up), never for one
+// 128x128 tile of a shorter k.
+inline bool gemm_plan_wide_ok(int64_t M, int64_t N, int64_t K) { return K >= 512 || M > 128 || N > 128; }
 
 // Scratch bytes for a split-K contraction.
 inline size_t gemm_split_ws_bytes(int64_t M, int64_t N, int64_t batch, int splits) {
@@ -190,8 +197,10 @@ void launch_wide_reduce(const GemmGroup& grp, hipStream_t st);
 // most one input gradient (A k-contiguous, B outer-contiguous, with a
 // residual).  Returns how many of them the group takes (all, or all but the
 // input gradient; 0: none), where the wide kernel takes them, no entry of
-// the running plan names one of them and the schedule is expected to be
-// shorter than one launch each.
+// the running plan names another kernel than the 256x256 wide one for a
+// weight gradient (or different split factors for them; the input gradient
+// is left out where an entry names another kernel) and the schedule is
+// expected to be shorter than one launch each.
 int plan_gemm_group(int dtype, const GemmArgs* gs, int n, GemmGroup* grp);
 // Launches a planned group; gemm_rowsum_parts() is that of gs[0].
 int launch_gemm_group(int dtype, const GemmGroup& grp, hipStream_t st);
