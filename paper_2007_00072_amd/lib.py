@@ -385,6 +385,13 @@ class Plan:
             _f["plan_destroy"](h)
 
 
+def plan_cfg_ok(key, tile_cfg: int) -> bool:
+    """Whether a plan entry for this contraction (ContractChoice.key()) may
+    name tile_cfg."""
+    M, N, K = key[:3]
+    return 0 <= tile_cfg <= 25 or (26 <= tile_cfg <= 28 and (K >= 512 or M > 128 or N > 128))
+
+
 def plan_log(on: bool) -> None:
     _call("plan_log", 1 if on else 0)
 

@@ -39,7 +39,7 @@ import time
 from collections import OrderedDict, defaultdict
 from typing import Dict, List, Sequence, Tuple
 
-TILE_CFGS = list(range(26))
+TILE_CFGS = list(range(29))
 # A measured difference smaller than the run-to-run spread of these timings
 # does not move a contraction off the library's own choice.
 KEEP_BUILTIN = 0.97
@@ -190,10 +190,9 @@ class _Layer:
             tot[canonical(lab)] += ms
         return {k: v / reps for k, v in tot.items()}
 
-    def launches(self):
-        """(label, ContractChoice) of every contraction one step launches by
-        itself (a plan's entry for one of a group's would end the group)."""
-        from . import dataflow, lib
+    def records(self):
+        """The contractions one step launches, as they ran."""
+        from . import lib
         lib.dm_trace_enable(True)
         lib.plan_log(True)
         self.step()
@@ -201,7 +200,32 @@ class _Layer:
         recs = lib.plan_log_read()
         lib.plan_log(False)
         lib.dm_trace_enable(False)
-        return [(canonical(r.label.decode()), r) for r in recs if r.label.decode() not in dataflow.GROUPED]
+        return recs
+
+    def launches(self):
+        """(label, ContractChoice) of every contraction one step launches by
+        itself (a plan's entry with another kernel for one of a group's would
+        end the group)."""
+        from . import dataflow
+        return [(canonical(r.label.decode()), r) for r in self.records() if r.label.decode() not in dataflow.GROUPED]
+
+    def step_ms(self, plans, reps: int):
+        """Median ms of a step under each plan (arguments of `use`), the
+        plans timed in turn."""
+        cuda = self.torch.cuda
+        times = [[] for _ in plans]
+        for _ in range(7):
+            for args, t in zip(plans, times):
+                self.use(*args)
+                self.step()
+                a, b = cuda.Event(enable_timing=True), cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(5 * reps):
+                    self.step()
+                b.record()
+                cuda.synchronize()
+                t.append(a.elapsed_time(b) / (5 * reps))
+        return [sorted(t)[len(t) // 2] for t in times]
 
 
 # Contractions that take an element-wise operator into their epilogue where
@@ -285,9 +309,6 @@ def tune(workload: str, reps: int = 3, log=print, shape=None, tile_cfgs=TILE_CFG
             L.use((), p, lay)
             tm = L.timed(reps)
             runs[(p, li)] = (tm, L.launches())
-    builtin_layout = {"ln_bwd_form": -1, "dO_transposed": -1, "dH_transposed": -1, "ln_lanes": -1}
-    L.use()
-    base = L.timed(reps)
     # stage names per run, fixed-cost stage times (averaged over the runs
     # that have the stage), and where each contraction shape occurs
     # (contractions are swept where they run under the library's own
@@ -335,6 +356,8 @@ def tune(workload: str, reps: int = 3, log=print, shape=None, tile_cfgs=TILE_CFG
         lay = combos[occurs_in[key]]
         seen = {}
         for cfg in tile_cfgs:
+            if not lib.plan_cfg_ok(key, cfg):
+                continue
             for sp in splits:
                 e = lib.ContractChoice(*key, cfg, sp)
                 L.use([e], 0, lay)
@@ -349,8 +372,8 @@ def tune(workload: str, reps: int = 3, log=print, shape=None, tile_cfgs=TILE_CFG
                 seen[eff] = sum(t for lab, t in tm.items() if names[lab] in sts)
         L.use((), 0, lay)
         builtin = next(((r.tile_cfg, r.splits) for lab, r in L.launches() if r.key() == key), None)
-        # (the library's own choice may be a kernel that no entry names)
-        if builtin is not None and builtin[0] not in TILE_CFGS:
+        # (the library's own choice may not be among the candidates)
+        if builtin is not None and builtin not in seen:
             tm = L.timed(reps)
             seen[builtin] = sum(t for lab, t in tm.items() if stage_name(lab, lay) in sts)
         if builtin in seen:
@@ -412,27 +435,46 @@ def tune(workload: str, reps: int = 3, log=print, shape=None, tile_cfgs=TILE_CFG
     result["lane_table"] = {str(k): round(v, 4) for k, v in lane_times.items()}
     entries = []
     for key, (cfg, sp) in chosen.items():
-        if cfg not in TILE_CFGS:
+        if cfg not in tile_cfgs:
             continue
         e = lib.ContractChoice(*key, cfg, sp)
         e.label = ",".join(where[key]).encode()[:47]
         entries.append(e)
     result["attn_path"] = attn_path
     result["layout"] = layout
-    result["entries"] = [dict(M=e.M, N=e.N, K=e.K, batch=e.batch, dtype=e.dtype, a_kcontig=e.a_kcontig,
-                              b_kcontig=e.b_kcontig, tile_cfg=e.tile_cfg, splits=e.splits,
-                              label=e.label.decode()) for e in entries]
-    result["builtin_ms"] = sum(base.values())
+    result["entries"] = as_dicts(entries)
     # Q/K/V projection grouping (Sec. "Algebraic Fusion"), a property of the
     # layer: the grouping with the least projection time over both passes
     table = fusion_table(workload, reps, shape)
     result["qkv_fusion_table"] = table
     result["qkv_fusion"] = min(table, key=lambda f: table[f]["forward"] + table[f]["backward"])
-    L.use(entries, attn_path, layout)
-    result["planned_ms"] = sum(L.timed(reps).values())
+    result["builtin_ms"], result["planned_ms"] = L.step_ms([(), (entries, attn_path, layout)], reps)
     L.use()
+    # what the library itself runs, as a plan
+    result["own_entries"] = as_dicts([r for r in L.records() if lib.plan_cfg_ok(r.key(), r.tile_cfg)])
     result["tuning_seconds"] = round(time.time() - t0, 1)
     return result
+
+
+def as_dicts(entries) -> List[dict]:
+    """Plan entries as they are saved (one per contraction shape)."""
+    out = OrderedDict()
+    for e in entries:
+        out.setdefault(e.key(), dict(M=e.M, N=e.N, K=e.K, batch=e.batch, dtype=e.dtype, a_kcontig=e.a_kcontig,
+                                     b_kcontig=e.b_kcontig, tile_cfg=e.tile_cfg, splits=e.splits,
+                                     label=e.label.decode()))
+    return list(out.values())
+
+
+def to_save(result: dict) -> dict:
+    """The plan to save of a tuning run: what it selected where the whole
+    step is faster with it (stages timed one by one with events do not always
+    add up to a faster step), otherwise the library's own choices."""
+    plan = dict(result)
+    own = plan.pop("own_entries")
+    if plan["planned_ms"] >= plan["builtin_ms"]:
+        plan.update(entries=own, attn_path=0, qkv_fusion=0, layout={f: -1 for f in plan["layout"]})
+    return plan
 
 
 FUSIONS = {0: "QKV fused", 1: "QK fused", 2: "unfused"}
@@ -486,8 +528,9 @@ def main() -> int:
         ap.error("--out is required")
     res = tune(a.workload, a.reps, log=lambda s: print(s, flush=True))
     with open(a.out, "w") as f:
-        json.dump(res, f, indent=1)
-    print(f"built-in {res['builtin_ms']:.3f} ms, planned {res['planned_ms']:.3f} ms (sum of launches), "
+        json.dump(to_save(res), f, indent=1)
+    print(f"built-in {res['builtin_ms']:.3f} ms, planned {res['planned_ms']:.3f} ms a step"
+          f"{'' if res['planned_ms'] < res['builtin_ms'] else ' (saved: the built-in choices)'}, "
           f"attn_path {res['attn_path']}, layout {res['layout']}, {len(res['entries'])} entries, "
           f"{res['tuning_seconds']} s", flush=True)
     return 0

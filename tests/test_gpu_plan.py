@@ -117,12 +117,13 @@ def test_tuner_end_to_end(tmp_path):
 
 
 def test_saved_bert_base_plan_keeps_parity():
-    # the tuned BERT-base plan (long-k weight gradients split four ways on
-    # the 4-wave 256x256 kernel, several contractions on other tiles) at
-    # its full size: every planned contraction runs its entry's choice
+    # a BERT-base plan of the general kernels (long-k weight gradients split
+    # four ways on 256x256 ping-pong tiles, several contractions on other
+    # tiles), kept here for what it covers, at its full size: every planned
+    # contraction runs its entry's choice
     import os
     from paper_2007_00072_amd.inputs import WORKLOADS
-    path = os.path.join(os.path.dirname(tune.__file__), "plans", "bert_base_bf16.json")
+    path = os.path.join(os.path.dirname(__file__), "plans", "bert_base_bf16_split.json")
     plan, cplan = tune.load_plan(path)
     recs, _ = _launches(WORKLOADS["bert_base_bf16"], cplan)
     want = {(e["M"], e["N"], e["K"], e["batch"], e["dtype"], e["a_kcontig"], e["b_kcontig"]): (e["tile_cfg"], e["splits"])
@@ -131,6 +132,26 @@ def test_saved_bert_base_plan_keeps_parity():
     assert planned and all((r.tile_cfg, r.splits) == want[r.key()] for r in planned)
     assert any(r.splits > 1 for r in planned)
     check_encoder(WORKLOADS["bert_base_bf16"], plan=cplan, qkv_fusion=int(plan.get("qkv_fusion", 0)))
+
+
+@pytest.mark.parametrize("name", ["bert_base_bf16", "bert_large_f16", "bert_large_stack24_bf16"])
+def test_shipped_plans_run_their_entries(name):
+    # the plans in the package, at their full size: every planned contraction
+    # runs its entry's choice, and the results are the built-in choices' up
+    # to the order of fp32 sums (a rounding to bf16 taken the other way, over
+    # the layer)
+    import os
+    plan, cplan = tune.load_plan(os.path.join(os.path.dirname(tune.__file__), "plans", name + ".json"))
+    wl = WORKLOADS[name]
+    L0, _, _, _, y0, dx0 = run_encoder(wl)
+    recs, _ = _launches(wl, cplan)
+    want = {tuple(e[f] for f in ("M", "N", "K", "batch", "dtype", "a_kcontig", "b_kcontig")): (e["tile_cfg"], e["splits"])
+            for e in plan["entries"]}
+    assert set(want) <= {r.key() for r in recs}
+    assert all((r.tile_cfg, r.splits) == want.get(r.key(), (r.tile_cfg, r.splits)) for r in recs)
+    L1, _, _, _, y1, dx1 = run_encoder(wl, plan=cplan)
+    for a, b in [(y0, y1), (dx0, dx1)] + [(L0.grads[n], L1.grads[n]) for n in ("wq", "wo", "w1", "w2")]:
+        assert (a.float() - b.float()).norm() <= 5e-3 * b.float().norm()
 
 
 @pytest.mark.parametrize("name", ["bert_large_f16", "bert_base_bf16"])

@@ -16,6 +16,7 @@ import pytest
 def test_plan_entry_range(M, N, K, wide, cfg):
     from paper_2007_00072_amd import lib
     entry = lib.ContractChoice(M, N, K, 1, lib.DM_F16, 1, 1, cfg, 1)
+    assert lib.plan_cfg_ok(entry.key(), cfg) == (0 <= cfg <= (28 if wide else 25))
     if 0 <= cfg <= (28 if wide else 25):
         assert lib.Plan([entry], 0).handle
     else:

@@ -79,8 +79,13 @@ def test_saved_plans_are_well_formed():
         assert 0 <= int(plan["attn_path"]) <= 3 and int(plan.get("qkv_fusion", 0)) in (0, 1, 2)
         assert plan["entries"]
         for e in plan["entries"]:
-            assert 0 <= e["tile_cfg"] <= 25 and 1 <= e["splits"] <= 64, (path, e)
+            assert 0 <= e["tile_cfg"] <= 28 and 1 <= e["splits"] <= 64, (path, e)
             assert e["M"] > 0 and e["N"] > 0 and e["K"] > 0 and e["batch"] >= 1
+        # no plan is shipped that a whole step is slower with (the library's
+        # own choices written out are as fast as no plan)
+        slower = plan["planned_ms"] >= plan["builtin_ms"]
+        assert not slower or (plan["attn_path"] == 0 and set(plan["layout"].values()) == {-1})
+        tune.load_plan(path)
 
 
 def layout_case(rng):
