@@ -867,16 +867,20 @@ bool attn_fwd_ok(int dtype, int K, int D) {
 }
 
 namespace {
-// key tiles per block: 8 (256 keys) when K allows it and the grid still
-// has about one block per CU, else 4 (128 keys)
-// (the last block of a head may reach past the last key: 256-key blocks
-// only where they pad no more than 128-key ones)
-// (a causal mask leaves the blocks of one head unequal work: 128-key blocks,
-// two rounds of them filling up to the same length: 4 x 1024 tokens, 64
-// heads, 92 us with 256-key blocks)
+// key tiles per block: 8 (256 keys) where the last block of a head, which may
+// reach past the last key, pads no more than with 128-key blocks and the grid
+// still has about one block per CU, else 4 (128 keys).  A causal mask leaves
+// the blocks of one head unequal work, longest first: one round of 256-key
+// blocks ends with the first key block of a head, two rounds of 128-key ones
+// earlier (backward us, 256- against 128-key blocks: 64 heads of 1024 keys 109
+// against 96, 16 of 4096 386 / 316, 64 of 768 83 / 63), and from a second
+// round on the longer blocks balance as well and stage the query side half as
+// often (72 heads of 1024 keys 112 / 115, 112 of 768 100 / 110, 256 of 512
+// 106 / 125, 128 of 2048 516 / 642; 40 to 320 heads of 512 to 2048 keys: up to
+// 3 % slower at 288 to 384 blocks, 10 to 20 % faster from there on).
 int keys_kg(int B, int H, int K, int causal) {
-    if (causal && K > 256) return 4;
-    return ((K + 255) / 256 * 256 == (K + 127) / 128 * 128 && (int64_t)B * H * ((K + 255) / 256) >= 192) ? 8 : 4;
+    const int64_t blocks = (int64_t)B * H * ((K + 255) / 256);
+    return ((K + 255) / 256 * 256 == (K + 127) / 128 * 128 && blocks >= (causal && K > 256 ? 288 : 192)) ? 8 : 4;
 }
 int keys_blocks(int K, int kg) { return (K + 32 * kg - 1) / (32 * kg); }
 AttnOp op_of(const AttnRows& r) { return attn_op(r.ptr, r.outer, r.inner, r.ld); }

@@ -83,12 +83,12 @@ PATHS = {
 }
 
 
-def key_blocks(s: Shape, dtype: str):
+def key_blocks(s: Shape, dtype: str, causal: bool = False):
     """Key-block backward of the shape: (possible, key blocks per head)."""
     if dtype == "f32" or s.P != 64 or s.W != 64 or s.K % 8:
         return False, 0
     n256, n128 = -(-s.K // 256), -(-s.K // 128)
-    eight = 2 * n256 == n128 and s.B * s.H * n256 >= 192
+    eight = 2 * n256 == n128 and s.B * s.H * n256 >= (288 if causal and s.K > 256 else 192)
     return True, n256 if eight else n128
 
 

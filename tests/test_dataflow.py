@@ -6,7 +6,7 @@ import os
 import pytest
 
 from paper_2007_00072_amd import dataflow
-from paper_2007_00072_amd.inputs import WORKLOADS
+from paper_2007_00072_amd.inputs import WORKLOADS, Shape
 
 GOLD = os.path.join(os.path.dirname(__file__), "golden", "table3_contraction_gflop.json")
 
@@ -100,3 +100,15 @@ def test_epilogue_and_folded_groups():
     # (3*T*I) read once less; the bias gradients (3*I) move with the pair
     assert (d0["fused_Melem"] - d1["fused_Melem"]) * 1e6 == pytest.approx(3 * T * F + 3 * T * s.I - 3 * s.I,
                                                                           abs=1e4)
+
+
+def test_key_blocks():
+    # 256-key blocks where they pad no more than 128-key ones and fill the
+    # CUs; under a causal mask only from a second round on
+    def blocks(B, H, K, causal=False):
+        return dataflow.key_blocks(Shape(B=B, J=K, K=K, H=H, P=64, W=64, I=64 * H, F=256), "f16", causal)
+    assert blocks(8, 16, 512) == (True, 2) and blocks(8, 16, 512, True) == (True, 4)
+    assert blocks(18, 16, 512, True) == (True, 2) and blocks(9, 16, 512, True) == (True, 2)
+    assert blocks(4, 16, 1024, True) == (True, 8) and blocks(12, 6, 1024, True) == (True, 4)
+    assert blocks(16, 12, 256, True) == (True, 1) and blocks(16, 12, 264) == (True, 3)
+    assert blocks(1, 1, 40) == (True, 1) and blocks(1, 1, 44)[0] is False

@@ -32,12 +32,16 @@ def test_mha_key_lengths(dtype, J, K):
     check_mha(wl, self_attention=False)
 
 
-def test_key_padding_leaves_neighbours_alone():
-    # 256-key blocks with the last one padded (240 blocks of one head each),
+@pytest.mark.parametrize("B,H,J,causal", [
+    (24, 8, 248, False),  # 192 blocks of 256 keys, one a head, padded
+    (18, 8, 392, True),   # 288 blocks, two a head, the second padded, steps before it left out
+    (17, 8, 392, True),   # the same on 128-key blocks
+])
+def test_key_padding_leaves_neighbours_alone(B, H, J, causal):
     # against the row form of the same backward
-    wl = small("bert_large_f16", B=24, J=248, K=248, H=8, P=64, W=64, I=512, F=512).with_(p_attn=0.1)
-    L0, _, _, _, y0, dx0 = run_encoder(wl)
-    L1, _, _, _, y1, dx1 = run_encoder(wl, plan=lib.Plan((), attn_path=1))
+    wl = small("bert_large_f16", B=B, J=J, K=J, H=H, P=64, W=64, I=64 * H, F=512).with_(p_attn=0.1)
+    L0, _, _, _, y0, dx0 = run_encoder(wl, causal=causal)
+    L1, _, _, _, y1, dx1 = run_encoder(wl, causal=causal, plan=lib.Plan((), attn_path=1))
     assert lib.attn_backward_form(L0.desc) and not lib.attn_backward_form(L1.desc)
     # the two forms round d(alpha) and P's products at different places
     assert (dx0.float() - dx1.float()).norm() <= 3e-3 * dx1.float().norm()
