@@ -553,13 +553,25 @@ int launch_gemm(int dtype, const GemmArgs& args, hipStream_t st) {
 }
 
 // ------------------------------------------------------------ groups
-// Expected times (us), from sweeps over K and the layers' own launches on
-// MI355X: a wide 256x256 tile takes 1.4 us per 64-wide k-step and 9 us for
-// its prologue and stores; the lean 128x128 kernel 0.57 us per step and
-// round of 256 tiles and 7 us; a launch costs about 3 us on top, and split
-// partials are written and read back at about 4 TB/s.
+// Expected times (us).  A wide 256x256 tile takes 1.4 us per 64-wide k-step
+// and 9 us for its prologue and stores (one round of a group in the encoder
+// backward, 1024 wide, 64 to 1024 tokens: 17.6 to 38.7 us, 1.41 a step and 16
+// fixed; 4096 tokens, every CU busy: 118); the 128x128 kernels 0.57 us per
+// step and round of 256 tiles and 7 us (the wide one there, 512 to 8192
+// tokens: 11.9 to 81.3 us, 0.54 a step and 7.6 fixed); a launch costs about
+// 3 us on top, and split partials are written and read back at about 4 TB/s.
+// Against the times measured (backward us, separate launches less the group,
+// 48 widths and token counts from 512 x 8192 to 2048 x 2048): where the model
+// expects more than 12 us from the group, it gives 14 to 250; below that its
+// sign is not to be trusted (expected 10.0 / 7.0 / 11.1 / 1.7 / 7.7 / 6.9 at
+// 896 x 1024, 960 x 512, 1088 x 768, 1088 x 1024, 1152 x 1536, 1280 x 1024:
+// measured -8 / -9 / -4 / -4 / +6 / +5), so separate launches keep those,
+// unless the token count is ragged (960 x 400: the general kernels that
+// separate launches then run are 40 us slower).  Which of the splits, and
+// whether the input gradient goes along, the same constants pick well (other
+// fits that describe each kernel better lost up to 12 % there).
 namespace {
-constexpr double WIDE_STEP = 1.4, WIDE_FIX = 9.0, LEAN_STEP = 0.57, LEAN_FIX = 7.0, LAUNCH = 3.0;
+constexpr double WIDE_STEP = 1.4, WIDE_FIX = 9.0, LEAN_STEP = 0.57, LEAN_FIX = 7.0, LAUNCH = 3.0, GROUP_MARGIN = 12.0;
 
 double ceil_div(double a, double b) { return (double)(int64_t)((a + b - 1) / b); }
 
@@ -640,7 +652,7 @@ int plan_gemm_group(int dtype, const GemmArgs* gs, int n, GemmGroup* grp) {
     // split factor of the weight gradients (the same for all), with and
     // without the input gradient in the grid
     const double tb = WIDE_STEP * ((kb + 63) / 64) + WIDE_FIX;
-    double best = separate;
+    double best = separate - (kw % 64 == 0 ? GROUP_MARGIN : 0.0);
     int best_s = 0, best_n = 0;
     for (int s = 1; s <= 4; ++s) {
         int64_t floats = 0, outs = 0;

@@ -124,3 +124,15 @@ def test_mha_on_wide_tiles(layout):
     wl = WORKLOADS["mha_large_f16"].with_(shape=Shape(B=5, J=104, K=104, H=8, P=64, W=64, I=512), layout=layout, p_attn=0.1)
     check_mha(wl, self_attention=True)
     check_mha(wl, self_attention=2)
+
+
+@pytest.mark.parametrize("shape,grouped", [
+    # 15 wide heads, 512 tokens: no more than a tie is expected, separate launches
+    (dict(B=4, J=128, K=128, H=15, P=64, W=64, I=960, F=3840), False),
+    # the same width on 400 (ragged) and 2048 tokens: one grid
+    (dict(B=2, J=200, K=200, H=15, P=64, W=64, I=960, F=3840), True),
+    (dict(B=16, J=128, K=128, H=15, P=64, W=64, I=960, F=3840), True),
+])
+def test_group_only_where_it_pays(shape, grouped):
+    _, labels = _launches(small("bert_base_bf16", **shape))
+    assert bool(grads_label(labels)) == grouped, labels
