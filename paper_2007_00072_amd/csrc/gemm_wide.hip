@@ -91,7 +91,9 @@ __device__ __forceinline__ void rowsum_mfma(floatx4& c, bf16x8 o, bf16x8 a) {
 // next MFMA): one wave issues an instruction every 4 cycles, so with its 16
 // an MFMA covers three others, and a copy with all of its scalar work in
 // one place held up the MFMAs (k-loop 26.0 against 22.5 us per 1024 of k
-// with outer-contiguous operands).
+// with outer-contiguous operands).  Neither statement tells the compiler of
+// m0, and before none of the assembly here does it insert wait states:
+// tests/test_wide_asm_cpu.py checks both in the assembly that it makes.
 __device__ __forceinline__ void set_m0(uint32_t slot, uint32_t ofs) {
     asm volatile("s_add_u32 m0, %0, %1" ::"s"(slot), "i"(ofs) : "scc", "memory");
 }
