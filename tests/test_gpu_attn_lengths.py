@@ -47,3 +47,25 @@ def test_key_padding_leaves_neighbours_alone(B, H, J, causal):
     assert (dx0.float() - dx1.float()).norm() <= 3e-3 * dx1.float().norm()
     for n in ("wq", "wk", "wv"):
         assert (L0.grads[n] - L1.grads[n]).norm() <= 3e-3 * L1.grads[n].norm(), n
+
+
+@pytest.mark.parametrize("name", ["bert_large_f16", "bert_base_bf16"])
+@pytest.mark.parametrize("J", [72, 136])
+def test_causal_on_separate_launches(name, J):
+    # QK^T, the masked softmax and Gamma one by one (and their backward), which
+    # a plan may ask for at any length and longer rows run by themselves
+    wl = small(name, B=2, J=J, K=J, H=4, P=64, W=64, I=256, F=512).with_(p_attn=0.1)
+    plan = lib.Plan((), attn_path=1)
+    _, labels = _launches(wl, plan)
+    assert {"F2 qkt", "F3 softmax", "F4 gamma", "B13 gamma_dx1", "B15 softmax_bwd"} <= set(labels), labels
+    check_encoder(wl, layer=1, causal=True, plan=plan)
+
+
+@pytest.mark.parametrize("name,causal", [("bert_large_f16", True), ("bert_base_bf16", True), ("bert_base_bf16", False)])
+def test_rows_beyond_the_chip(name, causal):
+    # 2056 keys: separate forward launches, the key-block backward on what
+    # they wrote (under the mask it leaves out blocks where P has to be zero)
+    wl = small(name, B=1, J=2056, K=2056, H=2, P=64, W=64, I=128, F=256).with_(p_attn=0.1)
+    _, labels = _launches(wl, None)
+    assert {"F2 qkt", "F3 softmax", "F4 gamma", "B13-17 score_bwd_keys"} <= set(labels), labels
+    check_encoder(wl, layer=1, causal=causal)

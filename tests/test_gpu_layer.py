@@ -254,8 +254,8 @@ def test_mha_fused_next_contraction(dtype, shape):
 
 @pytest.mark.parametrize("name,J", [("bert_large_f16", 96), ("bert_base_bf16", 96), ("bert_large_f16", 72)])
 def test_encoder_causal(name, J):
-    # decoder-style self-attention: J = 96 through the on-chip score kernels
-    # (a partial last row block), J = 72 through the two-launch softmax
+    # decoder-style self-attention through the on-chip score kernels: J = 96
+    # (three whole row blocks and key tiles), J = 72 (partial last ones)
     wl = small(name, B=2, J=J, K=J, H=4, P=64, W=64, I=256, F=512).with_(p_attn=0.1)
     check_encoder(wl, layer=1, causal=True)
 

@@ -2,8 +2,9 @@
 library's own choice for large outputs) and the grouped launch of the
 backward's weight gradients, at the sizes where they can go wrong: one, two
 and three k-steps (fewer than the five LDS slots hold), k-rows past the end
-of an outer-contiguous pair, ragged last tiles, split partials, every
-operand layout; and layers whose group is split, spread over several
+of an outer-contiguous pair, ragged last tiles, every operand layout; the
+128x128 tile from the eight k-steps on at which it is chosen, with split
+partials; and layers whose group is split, spread over several
 rounds, or takes the input gradient in."""
 import pytest
 import torch
@@ -17,20 +18,24 @@ pytestmark = pytest.mark.gpu
 DT = {"f16": (lib.DM_F16, torch.float16, 2.0 ** -11), "bf16": (lib.DM_BF16, torch.bfloat16, 2.0 ** -8)}
 
 
-def contraction(dtype, a_trans, b_trans, M, N, K, bias=False, out_f32=False, splits=1):
+def contraction(dtype, a_trans, b_trans, M, N, K, want, bias=False, out_f32=False, ws_parts=0):
+    """The library's own choice for these sizes: kernel and split factor
+    `want`, and the result.  ws_parts: scratch for that many partials."""
     code, td, _ = DT[dtype]
     A = make_tensor((K, M) if a_trans else (M, K), dtype, 3).cuda()
     B = make_tensor((N, K) if b_trans else (K, N), dtype, 4).cuda()
     bv = make_tensor((N,), dtype, 5).cuda() if bias else None
     # (a band of rows after the output that no store may reach)
     C = torch.full((M + 8, N), 7.0, dtype=torch.float32 if out_f32 else td, device="cuda")
-    ws = torch.empty(splits * M * N if splits > 1 else 1, dtype=torch.float32, device="cuda")
+    ws = torch.full((ws_parts * M * N + 8,), 7.0, dtype=torch.float32, device="cuda")
     lib.plan_log(True)
-    lib.contract(code, 1, M, N, K, 1.0, A, int(a_trans), 0, B, int(b_trans), 0, bv, C, int(out_f32), 0, -1, splits,
-                 ws if splits > 1 else None, ws.numel() * 4 if splits > 1 else 0)
+    lib.contract(code, 1, M, N, K, 1.0, A, int(a_trans), 0, B, int(b_trans), 0, bv, C, int(out_f32), 0, -1, 0,
+                 ws if ws_parts else None, ws_parts * M * N * 4)
     torch.cuda.synchronize()
+    ran = [(r.tile_cfg, r.splits) for r in lib.plan_log_read()]
     lib.plan_log(False)
-    assert (C[M:] == 7.0).all()
+    assert ran == [want], (ran, want)
+    assert (C[M:] == 7.0).all() and (ws[ws_parts * M * N:] == 7.0).all()
     a = (A.t() if a_trans else A).float()
     b = (B.t() if b_trans else B).float()
     ref = a.double() @ b.double().contiguous()
@@ -49,20 +54,45 @@ def contraction(dtype, a_trans, b_trans, M, N, K, bias=False, out_f32=False, spl
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("K", [64, 128, 192, 320])
 def test_wide_contract(dtype, a_trans, b_trans, K):
-    contraction(dtype, a_trans, b_trans, 3720, 3464, K, bias=True)
+    contraction(dtype, a_trans, b_trans, 3720, 3464, K, (26, 1), bias=True)
 
 
 @pytest.mark.parametrize("K", [8, 56, 72, 200, 328])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_wide_contract_ragged_k(dtype, K):
     # both operands outer-contiguous: the last step's missing k-rows are zeros
-    contraction(dtype, True, False, 3720, 3464, K, out_f32=dtype == "f16")
+    contraction(dtype, True, False, 3720, 3464, K, (26, 1), out_f32=dtype == "f16")
 
 
 @pytest.mark.parametrize("a_trans", [False, True])
 def test_wide_contract_192(a_trans):
     # 16 x 15 tiles of 256 x 192 fit one round where 256 x 256 leaves CUs idle
-    contraction("f16", a_trans, True, 4088, 2880, 256, bias=True)
+    contraction("f16", a_trans, True, 4088, 2880, 256, (27, 1), bias=True)
+
+
+# the 128x128 tile: 3 x 3 tiles with ragged last ones
+@pytest.mark.parametrize("a_trans,b_trans", [(False, True), (False, False), (True, True), (True, False)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K", [512, 576, 640])
+def test_mid_contract(dtype, a_trans, b_trans, K):
+    contraction(dtype, a_trans, b_trans, 264, 328, K, (28, 1), bias=True)
+    contraction(dtype, a_trans, b_trans, 8, 136, K, (28, 1), out_f32=True)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K", [520, 568, 584])
+def test_mid_contract_ragged_k(dtype, K):
+    contraction(dtype, True, False, 264, 328, K, (28, 1), out_f32=dtype == "f16")
+
+
+# split sums: pieces of eight steps, of nine with a last one of six, and (both
+# operands outer-contiguous) a last one that ends inside a step
+@pytest.mark.parametrize("a_trans,b_trans,K", [(False, True, 2048), (False, False, 2112), (True, True, 2112),
+                                               (True, False, 2048), (True, False, 2056)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_mid_contract_split(dtype, a_trans, b_trans, K):
+    contraction(dtype, a_trans, b_trans, 264, 328, K, (28, 4), bias=True, ws_parts=4)
+    contraction(dtype, a_trans, b_trans, 264, 328, K, (28, 3), out_f32=True, ws_parts=3)
 
 
 def grads_label(labels):
@@ -90,6 +120,8 @@ def test_layer_with_grouped_weight_gradients(name, shape, want):
     # BERT-base widths, 12288 tokens: 108 tiles, so the token sums are split
     # and the grid has more than one round
     ("bert_base_bf16", dict(B=96, J=128, K=128, H=12, P=64, W=64, I=768, F=3072)),
+    # the same split over 5000 tokens, no multiple of 64
+    ("bert_base_bf16", dict(B=25, J=200, K=200, H=12, P=64, W=64, I=768, F=3072)),
 ])
 def test_group_and_separate_launches_agree(name, shape):
     # a plan entry that names one of the contractions separates the group
