@@ -70,6 +70,7 @@ bool lean_ok(const GemmArgs& g, int bks) {
 // long as both operands take the same.  Any map, ragged sizes (zeros past
 // M, N, K); the epilogue stores through the output maps.
 constexpr int F32_T = 32, F32_K = 64, F32_P = F32_K + 4;
+constexpr uint32_t F32_ROW = 1 << 22;  // most tiles in a row of the grid
 
 // Piece p (of 512) of a 32 x 64 operand step: 4 elements along k of row p /
 // 16 (k-contiguous), or 4 rows of k-row p / 8 (outer-contiguous).
@@ -102,7 +103,11 @@ __global__ __launch_bounds__(256) void gemm_f32(GemmArgs g) {
     __shared__ __attribute__((aligned(16))) float sb[F32_T * F32_P];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = (int)(blockIdx.x % g.tiles_m) * F32_T, n0 = (int)(blockIdx.x / g.tiles_m) * F32_T;
+    // (tiles past the last one, in a grid of several rows, lie past N: nothing
+    // is loaded or stored there; a branch around them cost 0.7 us a launch, a
+    // row length from the arguments 0.4)
+    const uint32_t tile = blockIdx.z * F32_ROW + blockIdx.x;
+    const int m0 = (int)(tile % g.tiles_m) * F32_T, n0 = (int)(tile / g.tiles_m) * F32_T;
     const uint32_t z = blockIdx.y;
     int dummy = 0;
     const int64_t aoff = map_off(g.a.batch, z, 1, &dummy);
@@ -527,7 +532,12 @@ int launch_gemm(int dtype, const GemmArgs& args, hipStream_t st) {
         g.tiles_n = (g.N + F32_T - 1) / F32_T;
         if ((int64_t)((g.M + 63) / 64) * g.batch > 65535)
             return set_error(DM_ERR_UNSUPPORTED, "fp32 contraction grid too large");
-        dim3 grid((unsigned)g.tiles_m * g.tiles_n, g.batch);
+        // (a grid holds less than 2^32 threads along x, 68 GB of output: more
+        // tiles go in several rows; the indexes past the last tile fit too)
+        const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n, rows = (tiles + F32_ROW - 1) / F32_ROW;
+        if (rows > 512 || (rows * F32_ROW / g.tiles_m + 1) * F32_T > INT32_MAX)
+            return set_error(DM_ERR_UNSUPPORTED, "fp32 contraction grid too large");
+        dim3 grid((unsigned)std::min<int64_t>(tiles, F32_ROW), g.batch, (unsigned)rows);
         hipLaunchKernelGGL(gemm_f32, grid, dim3(256), 0, st, g);
         g.cfg = -1;
         log_launch(g, dtype);

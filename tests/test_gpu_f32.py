@@ -26,3 +26,19 @@ def test_f32_contract_edges(a_trans, b_trans, batch, M, N, K):
     # K fp32 products of magnitude ~1 added in fp32: error <= K u times the sum of magnitudes
     bound = 2.0 ** -23 * (K * 0.5 * torch.matmul(a.abs(), b.abs()) + ref.abs() + 1)
     assert ((C[:batch * M * N].view(batch, M, N).double() - ref).abs() <= bound).all()
+
+
+def test_f32_contract_many_tiles():
+    # 131070 x 129 tiles: 2^24 and more blocks of 256 threads, which one row of
+    # a grid does not hold; sampled rows against float64
+    M, N, K = 131070 * 32, 129 * 32, 4
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 70 GB")
+    A, B = make_tensor((M, K), "f32", 21).cuda(), make_tensor((N, K), "f32", 22).cuda()
+    C = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+    lib.contract(lib.DM_F32, 1, M, N, K, 1.0, A, 0, 0, B, 1, 0, None, C, 1, 0)
+    torch.cuda.synchronize()
+    for r in (0, 31, 1 << 20, M - 100, M - 33, M - 1):
+        ref = B.double() @ A[r].double()
+        bound = 2.0 ** -22 * (B.double().abs() @ A[r].double().abs())
+        assert ((C[r].double() - ref).abs() <= bound).all(), r
