@@ -13,9 +13,16 @@ from test_gpu_layer import DEV, small
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("name", ["bert_large_f16", "bert_base_bf16"])
-def test_encoder_step_graph_replays_match_eager(name):
-    wl = small(name, B=2, J=128, K=128, H=4, P=64, W=64, I=256, F=1024)
+@pytest.mark.parametrize("name,shape", [
+    ("bert_large_f16", dict(B=2, J=128, K=128, H=4, P=64, W=64, I=256, F=1024)),
+    ("bert_base_bf16", dict(B=2, J=128, K=128, H=4, P=64, W=64, I=256, F=1024)),
+    # score tiles above 64 KB of LDS (asked for at each launch), split sums
+    ("bert_base_bf16", dict(B=1, J=1096, K=1096, H=4, P=64, W=64, I=256, F=1024)),
+    # the grouped weight gradients
+    ("bert_large_f16", dict(B=4, J=128, K=128, H=16, P=64, W=64, I=1024, F=4096)),
+])
+def test_encoder_step_graph_replays_match_eager(name, shape):
+    wl = small(name, **shape)
     L = EncoderLayer(desc_for(wl, 1), make_params(wl, layer=1), DEV)
     x = make_activation(wl, 0).to(DEV)
     dy = make_activation(wl, 1).to(DEV)
