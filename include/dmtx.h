@@ -385,7 +385,9 @@ typedef struct {
 typedef struct {
     int32_t dO_transposed;  /* 1: the LayerNorm-2 backward also writes dO^T ([I][T]) and the    */
                             /* Linear-2 weight gradient reads it (column-split form only);     */
-                            /* 0: not.  Library: 1 wherever the column-split form runs          */
+                            /* 0: not.  Library: 1 where the column-split form runs, the        */
+                            /* weight gradients are launched one by one and the token count is */
+                            /* a multiple of 64 or below 512; else 0                            */
     int32_t dH_transposed;  /* 1: the activation backward also writes dH^T ([F][T]) and the    */
                             /* Linear-1 weight gradient reads it (16-bit types); 0: not.        */
                             /* Library: 0                                                       */

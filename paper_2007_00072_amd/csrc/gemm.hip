@@ -258,8 +258,9 @@ void choose(GemmArgs& g) {
                 want_split = (int)std::min<int64_t>(small ? 8 : 4, CUS / t);
                 min_k = small ? 128 : 192;
             }
-            // the wide kernels' 128x128 tile, from the five 64-wide steps
-            // on that its LDS slots hold
+            // the wide kernels' 128x128 tile from k = 512 on (eight 64-wide
+            // steps; its LDS slots hold five); split, a piece may have as few
+            // as two steps
             if (g.splits <= 1 && g.K >= 512 && gemm_wide_ok(g, 128)) g.cfg = GEMM_CFG_MID;
         }
     }
@@ -474,9 +475,6 @@ int plan_log_copy(dm_contract_choice* out, int cap) {
     return (int)t_log.size();
 }
 
-// Validation, plan and configuration of a 16-bit contraction; `pair`: when
-// no plan entry fixes the configuration, ask for the lean 128x128 kernel
-// unsplit (what a paired launch runs).
 // The same contraction with its outputs transposed (C^T = B^T A^T): the
 // operands and the output indexes trade places.
 static GemmArgs transposed(const GemmArgs& x) {
@@ -491,6 +489,9 @@ static GemmArgs transposed(const GemmArgs& x) {
     return g;
 }
 
+// Validation, plan and configuration of a 16-bit contraction; `pair`: when
+// no plan entry fixes the configuration, ask for the lean 128x128 kernel
+// unsplit (what a paired launch runs).
 static int prepare(GemmArgs& g, int dtype, bool pair) {
     if (g.K % 8 || g.M % 8 || g.N % 8)
         return set_error(DM_ERR_UNSUPPORTED, "contraction sizes must be multiples of 8");

@@ -71,8 +71,9 @@ struct Epilogue {
     // rows of rsum (row stride rsum_ld >= M, at most rsum_cap rows); the sum
     // of partial rows 0 .. n-1 at column m is row m of A summed over k, with
     // n = gemm_rowsum_parts() after the launch (0: not produced, and rsum
-    // untouched).  Only the lean 256x256 and 128x128 tiles, unsplit, with A
-    // outer-contiguous produce them.
+    // untouched).  Only the lean 256x256 and 128x128 tiles and the wide
+    // 128x128 one, unsplit, and the grouped launch's first contraction, each
+    // with A outer-contiguous, produce them.
     float* rsum;
     int rsum_ld;
     int rsum_cap;
@@ -85,7 +86,7 @@ struct Epilogue {
     // (dA rounded first, dH rounded as stored), and the partial column sums
     // of the stored dH go to rows of act_part (N floats each, at most
     // act_part_cap rows; gemm_act_parts() tells how many were written).
-    // Only the staged epilogue of the lean kernels does this
+    // Only the staged epilogues of the lean and the wide kernels do this
     // (gemm_act_fusable tells beforehand).
     int act_mode;
     void* act_out;

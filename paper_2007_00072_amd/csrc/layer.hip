@@ -107,12 +107,15 @@ void plan_attention(const Dims& x, int mode, Carver& sv, Carver& fw, Carver& bw,
     }
     p.prob = sv.take(es * x.S);
     p.gamma = sv.take(es * x.Tq * x.H * x.W);
+    // (for the key-block backward, whatever plan the forward runs under: the
+    // backward may run under another one)
     p.gamma32 = attn_keys_ok(x.dtype, (int)x.K, (int)x.P, (int)x.W, 0) ? sv.take(4 * x.Tq * x.H * x.W) : 0;
     p.beta = fw.take(es * x.S);
     p.alpha_f = fw.take(es * x.S);
     p.dgamma = bw.take(es * x.Tq * x.H * x.W);
-    // (dQ partials of the key-block backward: at most 4 B x 64 per query
-    // row and 128-key block, no more than 2 B per score)
+    // (dQ partials of the key-block backward: 4 B x 64 per query row and
+    // 128-key block, 2 B per score where 128 divides K; a padded last block
+    // takes more, 512 against 272 B per row at 136 keys)
     p.dalpha = bw.take(es * x.S > attn_keys_part_bytes((int)x.B, (int)x.H, (int)x.J, (int)x.K, x.causal)
                            ? es * x.S
                            : attn_keys_part_bytes((int)x.B, (int)x.H, (int)x.J, (int)x.K, x.causal));
@@ -444,7 +447,7 @@ int attention_core_fwd(const Dims& x, float scaler, const DropParams& dp, const 
 }
 
 // out(t, i) = sum_{h,w} gamma[t][(h,w)] wo[w][h][i] (+ bo)
-// (parts: the caller's next kernel sums split partials, see split_of)
+// (parts: the caller's next kernel sums split partials, see split_gemm)
 int out_projection(const Dims& x, const void* gamma, const void* wo, const void* bo, void* out, int layout,
                    hipStream_t st, SplitSum* parts = nullptr) {
     const int64_t HW = x.H * x.W;
@@ -864,7 +867,11 @@ int encoder_layer_bwd(const dm_layer_desc* d, const dm_layer_params* prm, const 
     const int grouped = x.qkv_fusion == 0 && fl.dO_t != 1 && !fl.dH_t ? plan_gemm_group(dt, tail, 5, &group) : 0;
     // (the library's own choice not for long ragged token sums: the wide
     // kernels take a k that is no multiple of 64 only with both operands
-    // outer-contiguous; 1000 tokens: 12 us against 27 for the general kernel)
+    // outer-contiguous.  Backward us without and with dO^T, separate
+    // launches, widths 512 / 768 / 1024: 520 tokens 155 and 165 / 166 and 178
+    // / 174 and 188, 1000 tokens 153 and 170 / 168 and 187 / 183 and 201, 4000
+    // tokens 235 and 251 / 304 and 360 / 400 and 455; 200 to 488 tokens and
+    // multiples of 64 from 256 to 4096: within 3 %)
     const bool have_dOT = !grouped && (fl.dO_t == 1 || (fl.dO_t == 2 && (T % 64 == 0 || T < 512)));
     l2.dsub_t = have_dOT ? dOT : nullptr;
     {

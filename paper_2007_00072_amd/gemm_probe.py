@@ -4,8 +4,9 @@
 
 For output shapes of the encoder layer's contractions (4096 tokens at
 BERT-large width: 4096 x 4096, the fused Q/K/V projection's 4096 x 3072
-and 4096 x 1024), times the library's lean kernels (`contract` with a
-fixed tile configuration) as the contraction length K grows, so the cost
+and 4096 x 1024), times the kernel that the library itself chooses (a wide
+one) and its lean kernels (`contract` with a fixed tile configuration), all
+unsplit, as the contraction length K grows, so the cost
 per k-step (the slope) separates from the fixed cost of launch, prologue
 and output stores (the intercept), next to torch.matmul on the same
 operands (the vendor BLAS of this PyTorch build, for reference only) and
@@ -50,7 +51,7 @@ def _slope(ks, us):
 def sweep(dev):
     rows = []
     ks = (512, 1024, 2048, 4096)
-    for M, N, cfgs in ((4096, 4096, (13, 20, 23, 24)), (4096, 3072, (23, 25)), (4096, 1024, (15, 18, 22))):
+    for M, N, cfgs in ((4096, 4096, (-1, 13, 20, 23, 24)), (4096, 3072, (-1, 23, 25)), (4096, 1024, (-1, 15, 18, 22))):
         C = torch.empty((M, N), device=dev, dtype=torch.float16)
         fill = _time(lambda: C.fill_(1.0))
         res = {"M": M, "N": N, "fill_us": fill, "cfg": {}}
@@ -77,7 +78,8 @@ def sweep(dev):
 
 def write(rows, copy_gbs, path, command):
     out = ["# Contraction sweep: fixed cost and cost per k-step (fp16)", "", "Command:", "", "```", command, "```", "",
-           "Lean kernels of the library (`contract`, fixed tile configuration, unsplit) against the contraction "
+           "The library's own choice (wide kernels: 256x256, 256x192 and 128x128 tiles) and its lean kernels "
+           "(`contract`, fixed tile configuration), unsplit, against the contraction "
            "length K at fixed output M x N; slope and intercept of a least-squares line through the four K.  "
            "`torch.matmul` (this PyTorch build's BLAS) on the same operands for reference.  `fill` is a plain "
            "fill of the output tensor.", "",
@@ -91,7 +93,8 @@ def write(rows, copy_gbs, path, command):
         out += [f"## M = {M}, N = {N} (output fill {r['fill_us']:.1f} us)", "",
                 "| kernel | " + " | ".join(f"K={k} (us)" for k in ks) + " | us per 1024 of K | TFLOP/s per k-step "
                 "| fixed (us) |", "|---|" + "---|" * (len(ks) + 3)]
-        series = [(f"cfg {c} ({names.get(c, '')})", v) for c, v in r["cfg"].items()] + [("torch.matmul", r["blas_us"])]
+        series = [("own choice" if c < 0 else f"cfg {c} ({names.get(c, '')})", v) for c, v in r["cfg"].items()]
+        series += [("torch.matmul", r["blas_us"])]
         for name, us in series:
             b, a = _slope(ks, us)
             tf = 2.0 * M * N / (b * 1e-6) / 1e12

@@ -50,6 +50,21 @@ def short_name(sym: str) -> str:
                 extra += f",act {val}"
         return (f"gemm_lean{m.group(1) or ''}<{dt},{m.group(3)}x{m.group(4)},waves {m.group(5)}x{m.group(6)},"
                 f"bk {m.group(7)},A:{mode(m.group(9))},B:{mode(m.group(10))}{extra}>")
+    # wide kernels: tile width, operand layouts, epilogue (mangled names, or as
+    # the demangler leaves the 128x128 ones)
+    eps = {"0": "", "1": ",act 1", "2": ",act 2", "3": ",residual", "4": ",float out"}
+    m = re.search(r"gemm_(wide|mid)I(?:DF16_|DF16b)(?:Li(\d+)E)?Lb(\d)ELb(\d)ELi(\d)E(?:Lb(\d)E)?", sym)
+    if m:
+        mode = lambda b: "k" if b == "1" else "o"
+        return (f"gemm_{m.group(1)}<{'256x' + m.group(2) if m.group(2) else '128x128'},A:{mode(m.group(3))},"
+                f"B:{mode(m.group(4))}{eps[m.group(5)]}{',row sums' if m.group(6) == '1' else ''}>")
+    m = re.search(r"gemm_mid<.*?(true|false), (\d), (true|false)>", sym)
+    if m:
+        return (f"gemm_mid<128x128,A:k,B:{'k' if m.group(1) == 'true' else 'o'}{eps[m.group(2)]}"
+                f"{',row sums' if m.group(3) == 'true' else ''}>")
+    m = re.search(r"gemm_wide_group|wide_group_reduce", sym)
+    if m:
+        return m.group(0)
     m = re.search(r"gemm_(x32|big)I(DF16_|DF16b)", sym)
     if m:
         return f"gemm_{m.group(1)}<{'f16' if m.group(2) == 'DF16_' else 'bf16'}>"
