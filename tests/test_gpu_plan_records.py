@@ -75,16 +75,18 @@ def test_entry_for_the_input_gradient_keeps_the_weight_gradients_together():
 
 
 @pytest.mark.parametrize("name", ["bert_large_f16", "bert_base_bf16"])
-@pytest.mark.parametrize("cfg", [26, 27, 28])
-def test_every_contraction_on_a_named_wide_kernel(name, cfg):
+@pytest.mark.parametrize("cfg,splits", [(26, 1), (27, 1), (28, 1), (26, 2), (27, 3), (28, 3)])
+def test_every_contraction_on_a_named_wide_kernel(name, cfg, splits):
     # k of 256 to 520 (four to nine 64-wide steps, the last of 8 k-rows),
     # ragged last tiles; what the kernel does not take (the input bias sums,
     # a ragged k next to an operand contiguous along it, a 192-wide operand
     # contiguous along its rows) falls back
     wl = small(name, B=5, J=104, K=104, H=4, P=64, W=64, I=256, F=512).with_(p_attn=0.1)
     recs, _ = _launches(wl)
-    plan = lib.Plan([lib.ContractChoice(*k, cfg, 1) for k in {r.key() for r in recs}], 0, {"dO_transposed": 0})
+    plan = lib.Plan([lib.ContractChoice(*k, cfg, splits) for k in {r.key() for r in recs}], 0, {"dO_transposed": 0})
     recs2, labels = _launches(wl, plan)
     ran = [r.tile_cfg for r in recs2]
     assert ran.count(cfg) >= (4 if cfg == 27 else 9), ran
+    # (Linear 2's partials, summed by the LayerNorm kernel, go down to two k-steps a piece)
+    assert splits == 1 or sum(r.splits == splits for r in recs2) >= 1, [(r.label, r.splits) for r in recs2]
     check_encoder(wl, layer=1, plan=plan)
